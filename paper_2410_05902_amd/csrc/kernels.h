@@ -5,6 +5,8 @@
 
 namespace mbkk {
 
+struct RescoreArgs;  // rescore.h
+
 // p[0 .. nwords) = v (32-bit words): the library's only way of clearing memory.
 void launch_fill32(void *p, uint32_t v, int64_t nwords, hipStream_t st);
 void launch_row_sqnorm(const float *X, int64_t n, int d, int64_t ld, float *sqn, unsigned int *sqmax,
@@ -29,9 +31,10 @@ void launch_prepare(const Layout &L, const Buffers &B, bool with_support, const 
 // waves), and the segment offsets of the support over those columns into
 // B.seg_next.  win: the window after the update and tau (> 0: the count
 // truncation of each center, whose dropped columns get coefficient 0).
+// resc: the listed rows to re-score first (NULL: none, or done already).
 void launch_update(const Layout &L, const Buffers &B, int b, int p_new, int p_expired, int init_alive_before,
                    int init_keep, const SlotList &live, const WindowRank &win, int lr, uint32_t gram_mask,
-                   int gram_ta, int gram_te, int gram_qmax, int gram_nwaves, hipStream_t st);
+                   int gram_ta, int gram_te, int gram_qmax, int gram_nwaves, const RescoreArgs *resc, hipStream_t st);
 
 // Gram blocks of slot rr against the columns in col_mask: plan (when not made
 // by the update), then work and fold.  mfma: the Gaussian MFMA forms (FP32
@@ -57,6 +60,13 @@ void launch_cross_mfma(const Layout &L, const Buffers &B, int nb, int precision,
 void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64, int mfma,
                   int precision, double tie_delta, double ymax2, double *D_out, int64_t ldD, bool with_rank,
                   hipStream_t st);
+// The rows that launch_score lists for re-scoring in the BF16 forms: every
+// such scoring is followed, before its results are used, by launch_rescore or
+// (with_rank) by an update that update_rescores admits, with the same arguments.
+RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precision, double kappa, double *D_out,
+                         int64_t ldD, bool with_rank);
+void launch_rescore(const Layout &L, const RescoreArgs &R, hipStream_t st);
+bool update_rescores(const Layout &L, int b, int gram_ta, int gram_te);  // (packed layouts)
 void launch_sum_mind(const Buffers &B, int nb, int accumulate, hipStream_t st);
 // Bound on the error of a self norm N_j of the Gaussian MFMA forms (FP32
 // kernel values summed in FP64), for row stride dp, max ||y||^2 and kappa.

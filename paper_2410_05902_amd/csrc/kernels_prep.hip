@@ -8,6 +8,7 @@
 //     kernels_gram.hip).
 #include "dev_common.h"
 #include "kernels.h"
+#include "rescore.h"
 
 namespace mbkk {
 
@@ -862,16 +863,27 @@ __global__ __launch_bounds__(1024) void k_group_offsets(
 // chunk sums of the counts are split over kGroupThreads / k slices of chunks.
 constexpr int kGroupSmallK = 512, kGroupSmallC = 8, kGroupThreads = 1024;
 
+// RS: the rows that the scoring listed for re-scoring are finished first, by
+// every workgroup of the launch (rescore_listed), and one of them goes on: a
+// launch of their own would cost each step 3 us, listed rows or not.
+// (gcnt, mind, labels and rank aren't restrict: the re-scoring writes them.)
+template <bool RS>
 __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
+    const RescoreArgs resc,
     int b, int k, int nchunk, int C, int p_new, int p_expired, int init_alive_before, int init_keep,
-    SlotList live, WindowRank win, int lr, const int32_t *__restrict__ gcnt, const float *__restrict__ mind,
+    SlotList live, WindowRank win, int lr, const int32_t *gcnt, const float *mind,
     double *__restrict__ coef, double *__restrict__ cum, int32_t *__restrict__ counts,
     double *__restrict__ alpha, int32_t *__restrict__ off, double *__restrict__ obj,
-    const int32_t *__restrict__ labels, const int32_t *__restrict__ rank, const int32_t *__restrict__ pts,
+    const int32_t *labels, const int32_t *rank, const int32_t *__restrict__ pts,
     int32_t *__restrict__ ring_idx, int32_t *__restrict__ ring_perm, uint32_t gram_mask, int gram_ta, int gram_te,
     int gram_qmax, int gram_nwaves, const int32_t *__restrict__ ring_off, int32_t *__restrict__ goff, int pad,
     int packed, int32_t *__restrict__ seg_next)
 {
+    if constexpr (RS) {
+        const int listed = resc.ctr[0];
+        if (__builtin_expect(listed > 0 || blockIdx.x != 0, 0) && !rescore_listed<2>(resc, listed))
+            return;
+    }
     constexpr int RPT = kMaxBatch / kGroupThreads;  // batch rows per thread
     // the task rows and columns are powers of two (the launch checks it)
     const int lta = __builtin_ctz((unsigned)gram_ta), lte = __builtin_ctz((unsigned)gram_te);
@@ -887,6 +899,13 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
     // is waited on before the next one is issued)
     int r_lab[RPT], r_rank[RPT], r_pt[RPT];
     float r_md[RPT];
+    const bool own = tid < k;
+    const int j = tid, jc = min(tid, k - 1);
+    double cf[kGroupSmallC];
+    int o0[kGroupSmallC], o1[kGroupSmallC];
+    double cumv = 0.0;
+    constexpr int CPT = kGroupLdsMax / kGroupThreads;
+    int v[CPT];
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
         const int pc = min(tid + i * nt, b - 1);  // b >= 1
@@ -895,11 +914,6 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
         r_pt[i] = pts[pc];
         r_md[i] = mind[pc];
     }
-    const bool own = tid < k;
-    const int j = tid, jc = min(tid, k - 1);
-    double cf[kGroupSmallC];
-    int o0[kGroupSmallC], o1[kGroupSmallC];
-    double cumv = 0.0;
     if ((tid & ~63) < k) {  // waves holding a center (one branch around every load)
 #pragma unroll
         for (int c = 0; c < kGroupSmallC; ++c) {
@@ -917,8 +931,6 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
             o0[c] = o1[c] = 0;
         }
     }
-    constexpr int CPT = kGroupLdsMax / kGroupThreads;
-    int v[CPT];
 #pragma unroll
     for (int q = 0; q < CPT; ++q)
         v[q] = gcnt[min(tid + q * nt, nchunk * k - 1)];
@@ -1143,9 +1155,21 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
     }
 }
 
+static bool update_small(const Layout &L, int b, int gram_ta, int gram_te)
+{
+    const bool pow2 = (gram_ta & (gram_ta - 1)) == 0 && (gram_te & (gram_te - 1)) == 0;
+    const int nchunk = (b + kChunk - 1) / kChunk;
+    return L.k <= kGroupSmallK && (int64_t)nchunk * L.k <= kGroupLdsMax && L.C <= kGroupSmallC && pow2;
+}
+
+bool update_rescores(const Layout &L, int b, int gram_ta, int gram_te)
+{
+    return L.packed && update_small(L, b, gram_ta, gram_te);
+}
+
 void launch_update(const Layout &L, const Buffers &B, int b, int p_new, int p_expired, int init_alive_before,
                    int init_keep, const SlotList &live, const WindowRank &win, int lr, uint32_t gram_mask,
-                   int gram_ta, int gram_te, int gram_qmax, int gram_nwaves, hipStream_t st)
+                   int gram_ta, int gram_te, int gram_qmax, int gram_nwaves, const RescoreArgs *resc, hipStream_t st)
 {
     const int nchunk = (b + kChunk - 1) / kChunk;
 #define MBKK_GO(LDS)                                                                                             \
@@ -1156,14 +1180,20 @@ void launch_update(const Layout &L, const Buffers &B, int b, int p_new, int p_ex
                        B.slot_pts + (int64_t)p_new * L.bmax, B.ring_idx + (int64_t)p_new * L.bmax,               \
                        B.ring_perm + (int64_t)p_new * L.bmax, gram_mask, gram_ta, gram_te, B.ring_off, B.goff, L.pad,  \
                        (int)L.packed, B.seg_next)
-    const bool pow2 = (gram_ta & (gram_ta - 1)) == 0 && (gram_te & (gram_te - 1)) == 0;
-    if (L.k <= kGroupSmallK && (int64_t)nchunk * L.k <= kGroupLdsMax && L.C <= kGroupSmallC && pow2)
-        hipLaunchKernelGGL(k_group_offsets_small, dim3(1), dim3(kGroupThreads), 0, st, b, L.k, nchunk, L.C, p_new,
-                           p_expired, init_alive_before, init_keep, live, win, lr, B.gcnt, B.mind, B.coef, B.cum,
-                           B.counts, B.alpha, B.ring_off + (int64_t)p_new * (L.k + 1), B.obj, B.labels, B.rank,
-                           B.slot_pts + (int64_t)p_new * L.bmax, B.ring_idx + (int64_t)p_new * L.bmax,
-                           B.ring_perm + (int64_t)p_new * L.bmax, gram_mask, gram_ta, gram_te, gram_qmax,
-                           gram_nwaves, B.ring_off, B.goff, L.pad, (int)L.packed, B.seg_next);
+#define MBKK_GOS(RS)                                                                                              \
+    hipLaunchKernelGGL(k_group_offsets_small<RS>, dim3(RS ? kRescoreWGs : 1), dim3(kGroupThreads), 0, st,         \
+                       RS ? *resc : RescoreArgs{}, b, L.k, nchunk, L.C, p_new, p_expired, init_alive_before,      \
+                       init_keep, live, win, lr, B.gcnt, B.mind, B.coef, B.cum, B.counts, B.alpha,                \
+                       B.ring_off + (int64_t)p_new * (L.k + 1), B.obj, B.labels, B.rank,                          \
+                       B.slot_pts + (int64_t)p_new * L.bmax, B.ring_idx + (int64_t)p_new * L.bmax,                \
+                       B.ring_perm + (int64_t)p_new * L.bmax, gram_mask, gram_ta, gram_te, gram_qmax,             \
+                       gram_nwaves, B.ring_off, B.goff, L.pad, (int)L.packed, B.seg_next)
+    if (update_small(L, b, gram_ta, gram_te)) {
+        if (resc)
+            MBKK_GOS(true);
+        else
+            MBKK_GOS(false);
+    }
     else if ((int64_t)nchunk * L.k <= kGroupLdsMax)
         MBKK_GO(true);
     else {
@@ -1171,6 +1201,7 @@ void launch_update(const Layout &L, const Buffers &B, int b, int p_new, int p_ex
                            B.gbase, B.counts);
         MBKK_GO(false);
     }
+#undef MBKK_GOS
 #undef MBKK_GO
 }
 

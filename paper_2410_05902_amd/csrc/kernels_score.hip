@@ -8,6 +8,7 @@
 #include "cross_layout.h"
 #include "dev_common.h"
 #include "kernels.h"
+#include "rescore.h"
 
 namespace mbkk {
 
@@ -27,50 +28,6 @@ __device__ __forceinline__ double self_kernel(int kind, double param, double sq)
     if (kind == MBKK_POLY2)
         return (sq + param) * (sq + param);
     return 1.0;  // normalised kernels: K(x,x) = 1
-}
-
-// LAYOUT 0: the direct kernel's runs (ranges of RR rows): run j (the run at
-// the center's first row) plus run k + r of every range r that starts
-// strictly inside the center's segment.
-// LAYOUT 1: the MFMA kernels write one partial per run of a center's blocks
-// inside a range of RB blocks, at the run's first block: the center's first
-// block and every range start inside the center.
-// LAYOUT 2 (packed segments, which may start inside a block): two slots per
-// block, 2 b for the run from block b's first row (a range start, or a center
-// starting there) and 2 b + 1 for a center starting inside block b; a
-// center's partials are its first slot and slot 2 b of every range start b
-// after its first block and inside its segment.
-// The direct kernel's runs are summed in FP64, the MFMA kernels' in FP32.
-template <typename T, int LAYOUT>
-__device__ __forceinline__ double cross_of(const T *__restrict__ part, int ldp, int row, int j,
-                                           const int32_t *__restrict__ seg_off, int RB, int k = 0)
-{
-    if constexpr (LAYOUT == 0) {
-        const int s0 = seg_off[j], s1 = seg_off[j + 1];
-        if (s0 >= s1)
-            return 0.0;
-        double s = (double)part[(int64_t)j * ldp + row];
-        for (int r = s0 / RB + 1; r * RB < s1; ++r)
-            s += (double)part[(int64_t)(k + r) * ldp + row];
-        return s;
-    } else if constexpr (LAYOUT == 1) {
-        const int bs = seg_off[j] / 32, be = seg_off[j + 1] / 32;
-        if (bs >= be)
-            return 0.0;
-        float s = part[(int64_t)bs * ldp + row];
-        for (int blk = (bs / RB + 1) * RB; blk < be; blk += RB)
-            s += part[(int64_t)blk * ldp + row];
-        return (double)s;
-    } else {
-        const int s0 = seg_off[j], s1 = seg_off[j + 1];
-        if (s0 >= s1)
-            return 0.0;
-        const int b0 = s0 / 32;
-        float s = part[(int64_t)(2 * b0 + (s0 % 32 != 0)) * ldp + row];
-        for (int blk = (b0 / RB + 1) * RB; 32 * blk < s1; blk += RB)
-            s += part[(int64_t)(2 * blk) * ldp + row];
-        return (double)s;
-    }
 }
 
 // cross_of in two phases, so that the loads of several centers are in
@@ -163,11 +120,6 @@ __device__ __forceinline__ double cross_finish(const CrossFetch<T> &f, const T *
 // lowest center index: comparisons are on (distance, label).
 constexpr int kScoreWaves = 16;
 
-__device__ __forceinline__ bool lex_less(double a, int la, double b, int lb)
-{
-    return a < b || (a == b && la < lb);
-}
-
 // One butterfly step of the per-row merge: the partner lane's (best, label,
 // second) by the DPP pattern CTRL, then the lexicographically smaller best
 // and the smallest remaining value as the second.
@@ -197,89 +149,15 @@ struct ScoreArgs {
     float *mind, *margin;
     double *Dout;
     int64_t ldD;
-    // FP64 re-scoring of near ties (BF16 forms): a fixed threshold (delta > 0)
+    // near ties (BF16 forms): a fixed threshold (delta > 0)
     // or the per-row bound from rel_dot, ymax2 and eN (the bound on the error
-    // of a self norm N_j); nresc counts the re-scored rows
+    // of a self norm N_j); R: see rescore.h
     double delta, kappa, rel_dot, ymax2, eN;
-    unsigned long long *nresc;
-    int d, dp;
-    const float *bat32, *pool32;
-    const int32_t *sup_row;
-    const double *sup_w64;
+    RescoreArgs R;
     // grouping ranks (iteration only): rank of each row among the equal
     // labels before it in its chunk of 64 rows, and the chunk's label counts
     int32_t *rank, *gcnt;
 };
-
-// FP64 re-scoring of one batch row by one wave: candidates are the centers
-// whose approximate distance is within delta of the best; for them the cross
-// term is recomputed in FP64 from the FP32 coordinates (direct ||x - y||^2,
-// FP64 exp, FP64 weights), and their distances (also in Dout when requested)
-// then carry only the error of N_j (FP32 kernel values summed in FP64).
-// best: the row's smallest approximate distance (from the scoring pass);
-// seg_off / Nv: the segment offsets and self norms (LDS copies when staged).
-template <int LAYOUT>
-__device__ void rescore_row(const ScoreArgs &A, int row, int RB, double delta, double best,
-                            const int32_t *__restrict__ seg_off, const double *__restrict__ Nv, int &lab_io,
-                            float &mind_io, float &margin_io)
-{
-    const int lane = threadIdx.x & 63;
-    const float *part = (const float *)A.part;
-    const float *x = A.bat32 + (int64_t)row * A.dp;
-    double b64 = INFINITY, s64 = INFINITY, outside = INFINITY;
-    int lab = 0;
-    for (int j0 = 0; j0 < A.k; j0 += 64) {
-        const int jl = j0 + lane;
-        const double Dap =
-            jl < A.k ? 1.0 - 2.0 * cross_of<float, LAYOUT>(part, A.ldp, row, jl, seg_off, RB) + Nv[jl] : INFINITY;
-        const bool cand = Dap <= best + delta;
-        if (!cand)
-            outside = fmin(outside, Dap);
-        uint64_t mask = __ballot(cand);
-        while (mask) {  // candidates in increasing center order (wave-uniform loop)
-            const int bit = __ffsll((unsigned long long)mask) - 1;
-            mask &= mask - 1;
-            const int j = j0 + bit;
-            double p = 0.0;
-            for (int s = seg_off[j] + lane; s < seg_off[j + 1]; s += 64) {
-                const double w = A.sup_w64[s];
-                if (w == 0.0)
-                    continue;
-                // rows are zero past d up to the padded stride: 16-byte loads over dp
-                const f32x4 *y4 = (const f32x4 *)(A.pool32 + (int64_t)A.sup_row[s] * A.dp);
-                const f32x4 *x4 = (const f32x4 *)x;
-                double d2 = 0.0;
-#pragma unroll 4
-                for (int t4 = 0; t4 < A.dp / 4; ++t4) {
-                    const f32x4 a = x4[t4], c = y4[t4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const double v = (double)a[u] - (double)c[u];
-                        d2 = fma(v, v, d2);
-                    }
-                }
-                p += w * exp(-d2 / A.kappa);
-            }
-            for (int o = 32; o > 0; o >>= 1)
-                p += __shfl_xor(p, o);
-            const double D = 1.0 - 2.0 * p + Nv[j];
-            if (A.Dout && lane == 0)
-                A.Dout[(int64_t)row * A.ldD + j] = D;  // replaces the approximate value
-            if (D < b64) {
-                s64 = b64;
-                b64 = D;
-                lab = j;
-            } else if (D < s64) {
-                s64 = D;
-            }
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1)
-        outside = fmin(outside, __shfl_xor(outside, o));
-    lab_io = lab;
-    mind_io = (float)b64;
-    margin_io = (float)(fmin(s64, outside) - b64);
-}
 
 // LK: the segment offsets and self norms are first copied to LDS (k <= kScoreLdsK).
 constexpr int kScoreLdsK = 2048;
@@ -294,7 +172,7 @@ __global__ __launch_bounds__(64 * kScoreWaves) void k_score(const ScoreArgs A)
     __shared__ int flab[64];
     __shared__ float fmin_[64], fmar[64];
     __shared__ double fdel[64], fbest[64], sep0[64];
-    __shared__ int smax_seg, snresc;
+    __shared__ int smax_seg, flist[kScoreWaves];
     __shared__ int32_t lseg[LK ? kScoreLdsK + 1 : 1];
     __shared__ double lN[LK ? kScoreLdsK : 1];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -368,10 +246,8 @@ __global__ __launch_bounds__(64 * kScoreWaves) void k_score(const ScoreArgs A)
     }
     if constexpr (RESCORE) {
         // longest center segment: the length of the FP32 sums in the error bound
-        if (threadIdx.x == 0) {
+        if (threadIdx.x == 0)
             smax_seg = 0;
-            snresc = 0;
-        }
         __syncthreads();
         int m = 0;
         for (int i = threadIdx.x; i < A.k; i += 64 * kScoreWaves)
@@ -472,28 +348,39 @@ __global__ __launch_bounds__(64 * kScoreWaves) void k_score(const ScoreArgs A)
     }
     __syncthreads();
     if constexpr (RESCORE) {
-        // the wave's rows w, w + 16, w + 32, w + 48, tested by lanes 0-3 at once
-        const int rt = w + kScoreWaves * (lane & 3);
-        uint64_t todo = __ballot(lane < 4 && blockIdx.x * 64 + rt < A.nb && (double)fmar[rt] < fdel[rt]);
-        while (todo) {  // wave-uniform row loop
-            const int r = w + kScoreWaves * (__ffsll((unsigned long long)todo) - 1);
-            todo &= todo - 1;
-            const int rw = blockIdx.x * 64 + r;
-            {
-                int l;
-                float m, g;
-                rescore_row<LAYOUT>(A, rw, RB, fdel[r], fbest[r], seg_off, Nv, l, m, g);
-                if (lane == 0) {
-                    flab[r] = l;
-                    fmin_[r] = m;
-                    fmar[r] = g;
-                    atomicAdd(&snresc, 1);
+        // every wave sees the same rows to re-score; the merge's LDS is free by now
+        static_assert(64 * (kScoreWaves + 1) >= kRescoreChunk && kScoreWaves <= kRescoreMaxWaves &&
+                          64 * kScoreWaves <= kRescoreChunk,
+                      "the merge arrays hold a pass's candidates");
+        uint64_t todo = __ballot(act && (double)fmar[lane] < fdel[lane]);
+        if (__builtin_expect(todo != 0, 0)) {  // workgroup uniform
+            const RescoreLds S{&sl[0][0], &sb[0][0], &ss[0][0], &flist[0]};
+            int nown = 0, room = kRescoreOwnEntries;
+            __syncthreads();  // the margins are read before the first row's is replaced
+            while (todo) {
+                const int r = __ffsll((unsigned long long)todo) - 1, rw = blockIdx.x * 64 + r;
+                todo &= todo - 1;
+                RescoreBest best;
+                double outside;
+                if (rescore_row<LAYOUT, true>(A.R, S, rw, fdel[r], fbest[r], RB, seg_off, Nv, 0, 0, 0, room, best,
+                                              outside)) {
+                    ++nown;
+                    if (threadIdx.x == 0) {
+                        flab[r] = best.l < A.k ? best.l : 0;
+                        fmin_[r] = (float)best.b;
+                        fmar[r] = (float)(fmin(best.s, outside) - best.b);
+                    }
+                } else if (threadIdx.x == 0) {
+                    // listed, with the approximate result standing in
+                    const int at = atomicAdd(&A.R.ctr[0], 1);
+                    A.R.list[at] = rw;
+                    A.R.delta[at] = fdel[r];
                 }
             }
+            __syncthreads();
+            if (threadIdx.x == 0 && nown > 0)
+                atomicAdd(A.R.nresc, (unsigned long long)nown);
         }
-        __syncthreads();
-        if (threadIdx.x == 0 && snresc > 0 && A.nresc)
-            atomicAdd(A.nresc, (unsigned long long)snresc);
     }
     if (w == 0 && act) {
         A.labels[row] = flab[lane];
@@ -538,6 +425,63 @@ double selfnorm_error_bound(int dp, double ymax2, double kappa)
     return (2.0 * (dp + 1) * u * ymax2 + 8.0 * u * ymax2) / kappa + 2.0 * u;
 }
 
+// The list lies in the differentiation form's per-row arrays (gr_perm, rowds),
+// the split rows' scratch in the seeding's (D2: at most 512 (row, part) pairs
+// of 16 sums, kself: at most 128 records): nothing else uses them between a
+// scoring pass and the launch that finishes its rows.  Data of less than 8192
+// rows has no room there and lists no row.
+RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precision, double kappa, double *D_out,
+                         int64_t ldD, bool with_rank)
+{
+    RescoreArgs R;
+    R.k = L.k;
+    R.dp = L.dp;
+    R.nb = nb;
+    R.RB = 2;
+    R.nranges = L.packed ? bs_nranges(nb, bs_mode(precision), L.dp) : 0;
+    R.ldp = L.bmax;
+    R.kappa = kappa;
+    R.part = (const float *)B.part;
+    R.bat32 = B.bat32;
+    R.pool32 = B.pool32;
+    R.seg_off = B.seg_off;
+    R.sup_row = B.sup_row;
+    R.sup_w64 = B.sup_w64;
+    R.N = B.N;
+    R.list = B.gr_perm;
+    R.delta = B.rowds;
+    R.ctr = B.rs_ctr;
+    static_assert(2 * kRescoreWGs * kRescoreMaxCand * 8 <= 8 * 8192 &&
+                      sizeof(RescoreRec) * (kRescoreWGs / 2) <= 8 * 8192,
+                  "the split rows' sums and records fit in the scratch of 8192 rows");
+    R.split = L.n >= 8192;
+    R.psum = B.D2;
+    R.rec = (RescoreRec *)B.kself;
+    R.labels = B.labels;
+    R.mind = B.mind;
+    R.margin = B.margin;
+    R.Dout = D_out;
+    R.ldD = ldD;
+    R.rank = with_rank ? B.rank : nullptr;
+    R.gcnt = B.gcnt;
+    R.nresc = B.nresc;
+    return R;
+}
+
+template <int LAYOUT>
+__global__ __launch_bounds__(kRescoreThreads) void k_rescore(const RescoreArgs A)
+{
+    (void)rescore_listed<LAYOUT>(A, A.ctr[0]);
+}
+
+void launch_rescore(const Layout &L, const RescoreArgs &R, hipStream_t st)
+{
+    if (L.packed)
+        hipLaunchKernelGGL(k_rescore<2>, dim3(kRescoreWGs), dim3(kRescoreThreads), 0, st, R);
+    else
+        hipLaunchKernelGGL(k_rescore<1>, dim3(kRescoreWGs), dim3(kRescoreThreads), 0, st, R);
+}
+
 void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64, int mfma,
                   int precision, double tie_delta, double ymax2, double *D_out, int64_t ldD, bool with_rank,
                   hipStream_t st)
@@ -571,13 +515,7 @@ void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double pa
                                          : 3.0 * 0x1p-16 + 3.0 * (double)L.dp * 0x1p-24;
     A.ymax2 = ymax2;
     A.eN = selfnorm_error_bound(L.dp, ymax2, param);
-    A.nresc = B.nresc;
-    A.d = L.d;
-    A.dp = L.dp;
-    A.bat32 = B.bat32;
-    A.pool32 = B.pool32;
-    A.sup_row = B.sup_row;
-    A.sup_w64 = B.sup_w64;
+    A.R = rescore_args(L, B, nb, precision, param, D_out, ldD, with_rank);
     A.rank = with_rank ? B.rank : nullptr;
     A.gcnt = B.gcnt;
     const bool rescore = precision == MBKK_BF16X3 || precision == MBKK_BF16X1;

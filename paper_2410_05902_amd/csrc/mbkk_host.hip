@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "kernels.h"
+#include "rescore.h"
 
 using namespace mbkk;
 
@@ -196,7 +197,8 @@ void carve(const Layout &Lc, char *base, Buffers &B)
     // device scalars and error flags, adjacent so that one copy reads both back
     B.obj = (double *)take(8 * 4 + 4 * 4);
     B.flags = (int32_t *)(B.obj + 4);
-    B.nresc = (unsigned long long *)take(8);
+    B.nresc = (unsigned long long *)take(8 + 2 * 4);
+    B.rs_ctr = (int32_t *)(B.nresc + 1);
     B.Nsig = (double *)take(8 * (size_t)L.k);
     B.dNsig = (double *)take(8 * (size_t)L.k);
     B.rowds = (double *)take(8 * (size_t)L.bmax);
@@ -421,6 +423,11 @@ static int timing_pair(mbkk_ctx *c, hipEvent_t *e0, hipEvent_t *e1)
     return MBKK_OK;
 }
 
+static bool step_rescores(const mbkk_ctx *c, int b)
+{
+    return c->L.bf16 && update_rescores(c->L, b, gram_task_rows(c->use_mfma), gram_task_cols(c->use_mfma, c->fp64));
+}
+
 static int cross_and_score(mbkk_ctx *c, int nb, double *D_out, int64_t ldD, bool with_rank)
 {
     const Layout &L = c->L;
@@ -442,6 +449,9 @@ static int cross_and_score(mbkk_ctx *c, int nb, double *D_out, int64_t ldD, bool
     }
     launch_score(L, c->B, nb, cf.kernel, cf.kernel_param, c->fp64, c->use_mfma, cf.precision, tie_delta(cf), c->ymax2,
                  D_out, ldD, with_rank, c->stream);
+    // rows listed for re-scoring: here, unless the update that follows runs them
+    if (L.bf16 && !(with_rank && step_rescores(c, nb)))
+        launch_rescore(L, rescore_args(L, c->B, nb, cf.precision, cf.kernel_param, D_out, ldD, with_rank), c->stream);
     HIPCHK(c, hipGetLastError());
     return MBKK_OK;
 }
@@ -492,7 +502,7 @@ static int setup(mbkk_ctx *c, const mbkk_config *cfg, void *workspace, void *str
     launch_fill32(c->B.sup_w + L.Mcap, 0, 1, c->stream);
     launch_fill32(c->B.sup_ay + L.Mcap, 0, 1, c->stream);
     launch_fill32(c->B.flags, 0, 4, c->stream);
-    launch_fill32(c->B.nresc, 0, 2, c->stream);
+    launch_fill32(c->B.nresc, 0, 2 + 2, c->stream);
     launch_fill32(c->B.ring_off, 0, (int64_t)L.P * (L.k + 1), c->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
@@ -793,9 +803,11 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
         win.rank[p] = -1;
     for (int q = 0; q < live_after.n; ++q)
         win.rank[live_after.r[q]] = q;
+    const bool resc = step_rescores(c, b);
+    const RescoreArgs ra = resc ? rescore_args(L, B, b, c->cfg.precision, c->cfg.kernel_param, nullptr, 0, true) : RescoreArgs{};
     launch_update(L, B, b, p_new, p_expired, init_alive_before, init_keep, live, win, c->cfg.lr, mask,
                   gram_task_rows(c->use_mfma), gram_task_cols(c->use_mfma, c->fp64), gram_task_qmax(c->use_mfma),
-                  gram_waves(c->use_mfma), c->stream);
+                  gram_waves(c->use_mfma), resc ? &ra : nullptr, c->stream);
     gram(c, p_new, mask, true);
     c->seg_next_iter = i + 1;
     HIPCHK(c, hipGetLastError());
@@ -1060,6 +1072,8 @@ int mbkk_objective_fwd(mbkk_ctx *c, const float *xb_dev, int32_t b, double sigma
     }
     launch_score(L, Bs, b, MBKK_GAUSS, kappa, c->fp64, c->use_mfma, cf.precision, tie_delta(cf), c->ymax2, nullptr, 0,
                  false, c->stream);
+    if (L.bf16)
+        launch_rescore(L, rescore_args(L, Bs, b, cf.precision, kappa, nullptr, 0, false), c->stream);
     launch_sum_mind(B, b, 0, c->stream);
     HIPCHK(c, hipGetLastError());
     if (labels_dev)

@@ -120,6 +120,7 @@ struct Buffers {
     double *obj = nullptr;       // [4] device scalars
     int32_t *flags = nullptr;    // [4] error flags (index, non-finite, label)
     unsigned long long *nresc = nullptr;  // [1] rows re-scored in FP64 (BF16 forms)
+    int32_t *rs_ctr = nullptr;   // [2] rows listed for re-scoring, workgroups done
     // differentiation form
     double *Nsig = nullptr;      // [k] self norms at the bandwidth of the call
     double *dNsig = nullptr;     // [k] their derivative
