@@ -13,7 +13,17 @@ namespace mbkk {
 // the same cut); a run is a range's stretch of one center's segment.  Run id:
 // the center j for the run that starts at the center's first row, k + r for
 // the run that starts at the start of range r inside a center.
-__host__ __device__ inline int direct_range_rows(int M, int nranges) { return (M + nranges - 1) / nranges; }
+// Small supports (direct_min_rows): a range holds at least kDirectMinRows
+// entries, whose terms are then summed in FP64 before the partial is stored.
+// The scoring reads a partial per range, and with b = 256, k = 3 (2-D blobs)
+// one-entry ranges gave it 340 per center to read, 65 us; with 8 it is 8 us and
+// the cross kernel no slower.
+constexpr int kDirectMinRows = 8;
+__host__ __device__ inline int direct_range_rows(int M, int nranges, int min_rows)
+{
+    const int r = (M + nranges - 1) / nranges;
+    return r > min_rows ? r : min_rows;
+}
 
 // Batch rows per lane of the direct kernel: two for FP32 rows of at most 32
 // coordinates (each broadcast support row then feeds two evaluations).
@@ -27,6 +37,13 @@ inline int direct_nranges(int nb, int rpl)
     const int tiles = (nb + 256 * rpl - 1) / (256 * rpl);
     const int r = (rpl == 2 ? kDirectWGs * 3 / 4 : kDirectWGs) / tiles;
     return r < 1 ? 1 : r;
+}
+
+// Fewest entries per range: kDirectMinRows where the fullest support has no
+// more per range anyway (so that every larger one keeps its cut), else 1.
+inline int direct_min_rows(const Layout &L, int nranges)
+{
+    return (L.Mcap + nranges - 1) / nranges <= kDirectMinRows ? kDirectMinRows : 1;
 }
 
 constexpr int kBsStageBlocks = 4;  // support blocks (32 rows) per stage of the MFMA kernel

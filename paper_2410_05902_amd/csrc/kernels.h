@@ -7,6 +7,14 @@ namespace mbkk {
 
 struct RescoreArgs;  // rescore.h
 
+// The caller's arrays that a scoring launch writes beside the library's own
+// (each may be NULL): labels, distances and margins [nb], every distance [nb x k].
+struct RowOutputs {
+    int32_t *labels = nullptr;
+    float *mind = nullptr, *margin = nullptr;
+    double *D = nullptr;
+};
+
 // p[0 .. nwords) = v (32-bit words): the library's only way of clearing memory.
 void launch_fill32(void *p, uint32_t v, int64_t nwords, hipStream_t st);
 void launch_row_sqnorm(const float *X, int64_t n, int d, int64_t ld, float *sqn, unsigned int *sqmax,
@@ -58,13 +66,13 @@ void launch_cross_mfma(const Layout &L, const Buffers &B, int nb, int precision,
 // per-row error bound of the form (tie_delta <= 0; ymax2 bounds ||y||^2 of
 // every support row), are re-scored in FP64.
 void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64, int mfma,
-                  int precision, double tie_delta, double ymax2, double *D_out, int64_t ldD, bool with_rank,
+                  int precision, double tie_delta, double ymax2, const RowOutputs &out, bool with_rank,
                   hipStream_t st);
 // The rows that launch_score lists for re-scoring in the BF16 forms: every
 // such scoring is followed, before its results are used, by launch_rescore or
 // (with_rank) by an update that update_rescores admits, with the same arguments.
-RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precision, double kappa, double *D_out,
-                         int64_t ldD, bool with_rank);
+RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precision, double kappa,
+                         const RowOutputs &out, bool with_rank);
 void launch_rescore(const Layout &L, const RescoreArgs &R, hipStream_t st);
 bool update_rescores(const Layout &L, int b, int gram_ta, int gram_te);  // (packed layouts)
 void launch_sum_mind(const Buffers &B, int nb, int accumulate, hipStream_t st);
@@ -97,7 +105,7 @@ void launch_grad_mfma(const Layout &L, const Buffers &B, int b, double sigma, co
 int dp_max_dim();
 void launch_dp_init(const Layout &L, const Buffers &B, int kind, double param, int fp64, hipStream_t st);
 void launch_dp_score(const Layout &L, const Buffers &B, int kind, double param, int fp64, const int32_t *idx, int m,
-                     bool step, double *D_out, int64_t ldD, int32_t *flags, hipStream_t st);
+                     bool step, const RowOutputs &out, int32_t *flags, hipStream_t st);
 void launch_dp_update(const Layout &L, const Buffers &B, int b, int kind, double param, int fp64, int lr,
                       hipStream_t st);
 // L.dp_mfma: the Gaussian FP32 form on MFMA (k_dp_mfma + k_dp_blend).

@@ -118,8 +118,10 @@ __device__ __forceinline__ double wave_bcast(double v, int e)
 // and the entries are then broadcast one by one, their rows read with
 // wave-uniform (scalar) loads, each used for the lane's RPL batch rows.  A
 // run ends where a center's segment ends.  Grid: (row tiles of 256 RPL) x (ranges).
-template <int KIND, typename T, int DR, int RPL>
-__global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int k, int nranges,
+// ACC: the type of a run's sum (FP64 for the FP32 form's small supports, see
+// direct_min_rows).
+template <int KIND, typename T, int DR, int RPL, typename ACC>
+__global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int k, int nranges, int min_rows,
                                                        const float *__restrict__ bat32,
                                                        const float *__restrict__ pool32,
                                                        const int32_t *__restrict__ sup_row,
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
     }
     const int r = blockIdx.y;
     const int M = seg_off[k];
-    const int RR = direct_range_rows(M, nranges);
+    const int RR = direct_range_rows(M, nranges, min_rows);
     const int s0 = r * RR, s1 = min(M, s0 + RR);
     if (s0 >= s1)
         return;  // block uniform
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
     int j = wave_segment_of(seg_off, k, s0);
     int cur_end = min(s1, seg_off[j + 1]);
     int id = s0 == seg_off[j] ? j : k + r;
-    T acc[RPL];
+    ACC acc[RPL];
 #pragma unroll
     for (int q = 0; q < RPL; ++q)
         acc[q] = 0;
@@ -175,7 +177,7 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
 #pragma unroll
                 for (int q = 0; q < RPL; ++q) {
                     if (row[q] < nb)
-                        P[(int64_t)id * ldp + row[q]] = acc[q];
+                        P[(int64_t)id * ldp + row[q]] = (T)acc[q];
                     acc[q] = 0;
                 }
                 do {
@@ -188,13 +190,13 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
             const T w = wave_bcast(lw, e);
             if constexpr (DR > 0) {
                 if constexpr (RPL == 1) {
-                    acc[0] = fma(w, kval_direct<KIND, T, DR>(x[0], y, cneg, prm), acc[0]);
+                    acc[0] = fma((ACC)w, (ACC)kval_direct<KIND, T, DR>(x[0], y, cneg, prm), acc[0]);
                 } else {
                     T kv[RPL];
                     kval_direct_rows<KIND, T, DR, RPL>(x, y, cneg, prm, kv);
 #pragma unroll
                     for (int q = 0; q < RPL; ++q)
-                        acc[q] = fma(w, kv[q], acc[q]);
+                        acc[q] = fma((ACC)w, (ACC)kv[q], acc[q]);
                 }
             } else {
                 // generic width: the batch row is re-read from memory
@@ -223,14 +225,14 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
                     T u = sacc + prm;
                     kv = u * u;
                 }
-                acc[0] = fma(w, kv, acc[0]);
+                acc[0] = fma((ACC)w, (ACC)kv, acc[0]);
             }
         }
     }
 #pragma unroll
     for (int q = 0; q < RPL; ++q)
         if (row[q] < nb)
-            P[(int64_t)id * ldp + row[q]] = acc[q];  // the last run (s0 < s1: it has entries)
+            P[(int64_t)id * ldp + row[q]] = (T)acc[q];  // the last run (s0 < s1: it has entries)
 }
 
 template <int KIND, typename T>
@@ -240,9 +242,17 @@ static void dispatch_direct_width(const Layout &L, const Buffers &B, int nb, int
     constexpr int R2 = sizeof(T) == 4 ? 2 : 1;  // rows per lane for d <= 32 (direct_rpl)
     const int rpl = direct_rpl(L.d, sizeof(T) == 8);
     dim3 grid((nb + 256 * rpl - 1) / (256 * rpl), nranges);
-#define MBKK_DIRECT_R(DR, RPL)                                                                                 \
-    hipLaunchKernelGGL((k_cross_direct<KIND, T, DR, RPL>), grid, dim3(256), 0, st, nb, L.d, L.dp, L.k, nranges, \
-                       B.bat32, B.pool32, B.sup_row, B.sup_w, B.sup_w64, B.seg_off, param, P, L.bmax)
+    const int min_rows = direct_min_rows(L, nranges);
+#define MBKK_DIRECT_A(DR, RPL, ACC)                                                                               \
+    hipLaunchKernelGGL((k_cross_direct<KIND, T, DR, RPL, ACC>), grid, dim3(256), 0, st, nb, L.d, L.dp, L.k, nranges, \
+                       min_rows, B.bat32, B.pool32, B.sup_row, B.sup_w, B.sup_w64, B.seg_off, param, P, L.bmax)
+#define MBKK_DIRECT_R(DR, RPL)           \
+    do {                                 \
+        if (min_rows > 1)                \
+            MBKK_DIRECT_A(DR, RPL, double); \
+        else                             \
+            MBKK_DIRECT_A(DR, RPL, T);   \
+    } while (0)
 #define MBKK_DIRECT(DR) MBKK_DIRECT_R(DR, (DR > 0 && DR <= 32 ? R2 : 1))
     if (L.d <= 4)
         MBKK_DIRECT(4);
@@ -258,6 +268,7 @@ static void dispatch_direct_width(const Layout &L, const Buffers &B, int nb, int
         MBKK_DIRECT(0);
 #undef MBKK_DIRECT
 #undef MBKK_DIRECT_R
+#undef MBKK_DIRECT_A
 }
 
 void launch_cross_direct(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64,

@@ -33,6 +33,7 @@
 
 #include "dev_common.h"
 #include "kernels.h"
+#include "rescore.h"
 
 namespace mbkk {
 
@@ -107,8 +108,8 @@ struct DpScoreArgs {
     const int32_t *idx;
     const double *N;
     double param;
-    int32_t *labels;
-    float *mind, *margin;
+    int32_t *labels, *labels_out;
+    float *mind, *margin, *mind_out, *margin_out;
     void *tsel;       // [m] old T[label][x] in the table type (may be NULL)
     int32_t *counts;  // [k] incremented per label (may be NULL)
     double *Dout;     // [m x ldD] every distance (may be NULL)
@@ -185,9 +186,7 @@ __global__ __launch_bounds__(64 * kDpScoreWaves) void k_dp_score(DpScoreArgs A)
         if (!(l0 >= 0 && l0 < A.k))
             l0 = 0;  // every distance NaN: keep the label in range
         if (act) {
-            A.labels[r] = l0;
-            A.mind[r] = (float)b0;
-            A.margin[r] = (float)(s0 - b0);
+            write_row(A, r, l0, (float)b0, (float)(s0 - b0));
             if (A.tsel)
                 ((TT *)A.tsel)[r] = T[(int64_t)l0 * A.ldT + x];
             if (A.counts)
@@ -933,7 +932,7 @@ static void dp_score_kind(DpScoreArgs &A, hipStream_t st)
 }
 
 void launch_dp_score(const Layout &L, const Buffers &B, int kind, double param, int fp64, const int32_t *idx, int m,
-                     bool step, double *D_out, int64_t ldD, int32_t *flags, hipStream_t st)
+                     bool step, const RowOutputs &out, int32_t *flags, hipStream_t st)
 {
     DpScoreArgs A;
     A.T = B.dp_T;
@@ -952,8 +951,11 @@ void launch_dp_score(const Layout &L, const Buffers &B, int kind, double param, 
     A.margin = B.margin;
     A.tsel = step ? B.dp_tsel : nullptr;
     A.counts = step ? B.counts : nullptr;
-    A.Dout = D_out;
-    A.ldD = ldD;
+    A.labels_out = out.labels;
+    A.mind_out = out.mind;
+    A.margin_out = out.margin;
+    A.Dout = out.D;
+    A.ldD = L.k;
     A.flags = flags;
 #define MBKK_DP_SCORE(TT)                                                             \
     switch (kind) {                                                                   \

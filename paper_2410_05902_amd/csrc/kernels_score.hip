@@ -91,8 +91,17 @@ __device__ __forceinline__ double cross_finish(const CrossFetch<T> &f, const T *
         double s = (double)f.a;
         if (f.next >= 0) {
             s += (double)f.b;
-            for (int r = f.next; r * RB < f.hi; ++r)
-                s += (double)part[(int64_t)(k + r) * ldp + row];
+            // eight partials' loads in flight, added in range order
+            const int top = (f.hi - 1) / RB;  // the segment's last range
+            for (int r0 = f.next; r0 <= top; r0 += 8) {
+                T v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    v[u] = part[(int64_t)(k + min(r0 + u, top)) * ldp + row];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    s += r0 + u <= top ? (double)v[u] : 0.0;
+            }
         }
         return s;
     } else if constexpr (LAYOUT == 1) {
@@ -138,15 +147,15 @@ __device__ __forceinline__ void score_merge_step(double &b0, int &l0, double &s0
 }
 
 struct ScoreArgs {
-    int nb, k, ldp, RB, kind;
+    int nb, k, ldp, RB, kind;  // RB: blocks per range of the general MFMA kernel; fewest rows per range of the direct one
     int nranges;  // > 0: RB of the batch-stationary kernel, derived from the support size
     double param;
     const void *part;
     const int32_t *seg_off;
     const double *N;
     const double *batsq64;
-    int32_t *labels;
-    float *mind, *margin;
+    int32_t *labels, *labels_out;
+    float *mind, *margin, *mind_out, *margin_out;
     double *Dout;
     int64_t ldD;
     // near ties (BF16 forms): a fixed threshold (delta > 0)
@@ -198,7 +207,7 @@ __global__ __launch_bounds__(64 * kScoreWaves) void k_score(const ScoreArgs A)
         nv0 = A.N[min(i, A.k - 1)];
     }
     const int mtot = A.seg_off[A.k];
-    const int RB = LAYOUT == 0 ? direct_range_rows(mtot, A.nranges)
+    const int RB = LAYOUT == 0 ? direct_range_rows(mtot, A.nranges, A.RB)
                                : (A.nranges > 0 ? bs_range_blocks(mtot / 32, A.nranges) : A.RB);
     CrossFetch<T> fe0[HOIST ? NB : 1];
     if constexpr (HOIST) {
@@ -383,9 +392,9 @@ __global__ __launch_bounds__(64 * kScoreWaves) void k_score(const ScoreArgs A)
         }
     }
     if (w == 0 && act) {
-        A.labels[row] = flab[lane];
-        A.mind[row] = fmin_[lane];
-        A.margin[row] = fmar[lane];
+        // the caller's arrays are written here: a copy after the launch took
+        // 5 us for each of them
+        write_row(A, row, flab[lane], fmin_[lane], fmar[lane]);
     }
     if (A.rank) {
         // rank of row r among the rows t < r of the chunk with its label, and
@@ -430,8 +439,8 @@ double selfnorm_error_bound(int dp, double ymax2, double kappa)
 // of 16 sums, kself: at most 128 records): nothing else uses them between a
 // scoring pass and the launch that finishes its rows.  Data of less than 8192
 // rows has no room there and lists no row.
-RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precision, double kappa, double *D_out,
-                         int64_t ldD, bool with_rank)
+RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precision, double kappa,
+                         const RowOutputs &out, bool with_rank)
 {
     RescoreArgs R;
     R.k = L.k;
@@ -460,8 +469,11 @@ RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precisio
     R.labels = B.labels;
     R.mind = B.mind;
     R.margin = B.margin;
-    R.Dout = D_out;
-    R.ldD = ldD;
+    R.labels_out = out.labels;
+    R.mind_out = out.mind;
+    R.margin_out = out.margin;
+    R.Dout = out.D;
+    R.ldD = L.k;
     R.rank = with_rank ? B.rank : nullptr;
     R.gcnt = B.gcnt;
     R.nresc = B.nresc;
@@ -483,16 +495,16 @@ void launch_rescore(const Layout &L, const RescoreArgs &R, hipStream_t st)
 }
 
 void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64, int mfma,
-                  int precision, double tie_delta, double ymax2, double *D_out, int64_t ldD, bool with_rank,
+                  int precision, double tie_delta, double ymax2, const RowOutputs &out, bool with_rank,
                   hipStream_t st)
 {
     ScoreArgs A;
     A.nb = nb;
     A.k = L.k;
     A.ldp = L.bmax;
-    A.RB = 2;
     A.nranges = mfma ? (L.dp <= 128 ? bs_nranges(nb, bs_mode(precision), L.dp) : 0)
                      : direct_nranges(nb, direct_rpl(L.d, fp64));
+    A.RB = mfma ? 2 : direct_min_rows(L, A.nranges);
     A.kind = kind;
     A.param = param;
     A.part = B.part;
@@ -502,8 +514,11 @@ void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double pa
     A.labels = B.labels;
     A.mind = B.mind;
     A.margin = B.margin;
-    A.Dout = D_out;
-    A.ldD = ldD;
+    A.labels_out = out.labels;
+    A.mind_out = out.mind;
+    A.margin_out = out.margin;
+    A.Dout = out.D;
+    A.ldD = L.k;
     A.delta = tie_delta;
     A.kappa = param;
     // relative error of the split product x.y against sum_t |x_t y_t|: bf16
@@ -515,7 +530,7 @@ void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double pa
                                          : 3.0 * 0x1p-16 + 3.0 * (double)L.dp * 0x1p-24;
     A.ymax2 = ymax2;
     A.eN = selfnorm_error_bound(L.dp, ymax2, param);
-    A.R = rescore_args(L, B, nb, precision, param, D_out, ldD, with_rank);
+    A.R = rescore_args(L, B, nb, precision, param, out, with_rank);
     A.rank = with_rank ? B.rank : nullptr;
     A.gcnt = B.gcnt;
     const bool rescore = precision == MBKK_BF16X3 || precision == MBKK_BF16X1;

@@ -428,7 +428,7 @@ static bool step_rescores(const mbkk_ctx *c, int b)
     return c->L.bf16 && update_rescores(c->L, b, gram_task_rows(c->use_mfma), gram_task_cols(c->use_mfma, c->fp64));
 }
 
-static int cross_and_score(mbkk_ctx *c, int nb, double *D_out, int64_t ldD, bool with_rank)
+static int cross_and_score(mbkk_ctx *c, int nb, const RowOutputs &out, bool with_rank)
 {
     const Layout &L = c->L;
     const mbkk_config &cf = c->cfg;
@@ -448,10 +448,10 @@ static int cross_and_score(mbkk_ctx *c, int nb, double *D_out, int64_t ldD, bool
         c->launches++;
     }
     launch_score(L, c->B, nb, cf.kernel, cf.kernel_param, c->fp64, c->use_mfma, cf.precision, tie_delta(cf), c->ymax2,
-                 D_out, ldD, with_rank, c->stream);
+                 out, with_rank, c->stream);
     // rows listed for re-scoring: here, unless the update that follows runs them
     if (L.bf16 && !(with_rank && step_rescores(c, nb)))
-        launch_rescore(L, rescore_args(L, c->B, nb, cf.precision, cf.kernel_param, D_out, ldD, with_rank), c->stream);
+        launch_rescore(L, rescore_args(L, c->B, nb, cf.precision, cf.kernel_param, out, with_rank), c->stream);
     HIPCHK(c, hipGetLastError());
     return MBKK_OK;
 }
@@ -731,7 +731,10 @@ static int dp_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels
     set_batch_view(c, 0);
     launch_gather_rows(B.X, L.n, L.d, B.ld, batch, b, L.dp, B.bat32, B.bathi, B.batlo, B.batsq, B.batsq64, B.batidx,
                        B.flags, cf.validate, c->stream);
-    launch_dp_score(L, B, cf.kernel, cf.kernel_param, c->fp64, B.batidx, b, true, nullptr, 0, nullptr, c->stream);
+    RowOutputs out;
+    out.labels = labels_dev;
+    out.mind = mind_dev;
+    launch_dp_score(L, B, cf.kernel, cf.kernel_param, c->fp64, B.batidx, b, true, out, nullptr, c->stream);
     launch_sum_mind(B, b, 0, c->stream);
     launch_dp_update(L, B, b, cf.kernel, cf.kernel_param, c->fp64, cf.lr, c->stream);
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -750,10 +753,6 @@ static int dp_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels
     c->slot_b[0] = b;
     c->iter += 1;
     c->version++;
-    if (labels_dev)
-        HIPCHK(c, hipMemcpyAsync(labels_dev, B.labels, 4 * (size_t)b, hipMemcpyDeviceToDevice, c->stream));
-    if (mind_dev)
-        HIPCHK(c, hipMemcpyAsync(mind_dev, B.mind, 4 * (size_t)b, hipMemcpyDeviceToDevice, c->stream));
     if (fbefore_host) {
         double s = 0.0;
         HIPCHK(c, hipMemcpyAsync(&s, B.obj + 1, sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -783,7 +782,10 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
     if (c->cfg.validate && clear_flags(c))
         return MBKK_E_HIP;
     prepare(c, batch, b);
-    int rc = cross_and_score(c, b, nullptr, 0, true);
+    RowOutputs out;
+    out.labels = labels_dev;
+    out.mind = mind_dev;
+    int rc = cross_and_score(c, b, out, true);
     if (rc)
         return rc;
     // update of the centers
@@ -804,7 +806,7 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
     for (int q = 0; q < live_after.n; ++q)
         win.rank[live_after.r[q]] = q;
     const bool resc = step_rescores(c, b);
-    const RescoreArgs ra = resc ? rescore_args(L, B, b, c->cfg.precision, c->cfg.kernel_param, nullptr, 0, true) : RescoreArgs{};
+    const RescoreArgs ra = resc ? rescore_args(L, B, b, c->cfg.precision, c->cfg.kernel_param, out, true) : RescoreArgs{};
     launch_update(L, B, b, p_new, p_expired, init_alive_before, init_keep, live, win, c->cfg.lr, mask,
                   gram_task_rows(c->use_mfma), gram_task_cols(c->use_mfma, c->fp64), gram_task_qmax(c->use_mfma),
                   gram_waves(c->use_mfma), resc ? &ra : nullptr, c->stream);
@@ -814,10 +816,6 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
     c->slot_b[p_new] = b;
     c->iter = i + 1;
     c->version++;
-    if (labels_dev)
-        HIPCHK(c, hipMemcpyAsync(labels_dev, B.labels, 4 * (size_t)b, hipMemcpyDeviceToDevice, c->stream));
-    if (mind_dev)
-        HIPCHK(c, hipMemcpyAsync(mind_dev, B.mind, 4 * (size_t)b, hipMemcpyDeviceToDevice, c->stream));
     if (fbefore_host) {
         double s = 0.0;
         HIPCHK(c, hipMemcpyAsync(&s, B.obj, sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -846,21 +844,20 @@ int mbkk_assign(mbkk_ctx *c, const int32_t *idx, int64_t m, int32_t *labels_dev,
         prepare(c, nullptr, 0);
     for (int64_t m0 = 0; m0 < m; m0 += L.bmax) {
         const int nb = (int)((m - m0) < L.bmax ? (m - m0) : L.bmax);
+        RowOutputs out;
+        out.labels = labels_dev ? labels_dev + m0 : nullptr;
+        out.mind = mind_dev ? mind_dev + m0 : nullptr;
+        out.margin = margin_dev ? margin_dev + m0 : nullptr;
+        out.D = D_dev ? D_dev + m0 * L.k : nullptr;
         if (L.untrunc) {
-            launch_dp_score(L, B, c->cfg.kernel, c->cfg.kernel_param, c->fp64, idx + m0, nb, false,
-                            D_dev ? D_dev + m0 * L.k : nullptr, L.k, c->cfg.validate ? B.flags : nullptr, c->stream);
+            launch_dp_score(L, B, c->cfg.kernel, c->cfg.kernel_param, c->fp64, idx + m0, nb, false, out,
+                            c->cfg.validate ? B.flags : nullptr, c->stream);
         } else {
             prepare(c, idx + m0, nb);
-            int rc = cross_and_score(c, nb, D_dev ? D_dev + m0 * L.k : nullptr, L.k, false);
+            int rc = cross_and_score(c, nb, out, false);
             if (rc)
                 return rc;
         }
-        if (labels_dev)
-            HIPCHK(c, hipMemcpyAsync(labels_dev + m0, B.labels, 4 * (size_t)nb, hipMemcpyDeviceToDevice, c->stream));
-        if (mind_dev)
-            HIPCHK(c, hipMemcpyAsync(mind_dev + m0, B.mind, 4 * (size_t)nb, hipMemcpyDeviceToDevice, c->stream));
-        if (margin_dev)
-            HIPCHK(c, hipMemcpyAsync(margin_dev + m0, B.margin, 4 * (size_t)nb, hipMemcpyDeviceToDevice, c->stream));
     }
     if (c->cfg.validate)
         return check_flags(c);
@@ -881,11 +878,11 @@ int mbkk_objective(mbkk_ctx *c, const int32_t *idx, int64_t m, double *out_host)
     for (int64_t m0 = 0; m0 < m; m0 += L.bmax) {
         const int nb = (int)((m - m0) < L.bmax ? (m - m0) : L.bmax);
         if (L.untrunc) {
-            launch_dp_score(L, c->B, c->cfg.kernel, c->cfg.kernel_param, c->fp64, idx + m0, nb, false, nullptr, 0,
+            launch_dp_score(L, c->B, c->cfg.kernel, c->cfg.kernel_param, c->fp64, idx + m0, nb, false, RowOutputs{},
                             c->cfg.validate ? c->B.flags : nullptr, c->stream);
         } else {
             prepare(c, idx + m0, nb);
-            int rc = cross_and_score(c, nb, nullptr, 0, false);
+            int rc = cross_and_score(c, nb, RowOutputs{}, false);
             if (rc)
                 return rc;
         }
@@ -1070,14 +1067,14 @@ int mbkk_objective_fwd(mbkk_ctx *c, const float *xb_dev, int32_t b, double sigma
         HIPCHK(c, hipEventRecord(e1, c->stream));
         c->launches++;
     }
-    launch_score(L, Bs, b, MBKK_GAUSS, kappa, c->fp64, c->use_mfma, cf.precision, tie_delta(cf), c->ymax2, nullptr, 0,
+    RowOutputs out;
+    out.labels = labels_dev;
+    launch_score(L, Bs, b, MBKK_GAUSS, kappa, c->fp64, c->use_mfma, cf.precision, tie_delta(cf), c->ymax2, out,
                  false, c->stream);
     if (L.bf16)
-        launch_rescore(L, rescore_args(L, Bs, b, cf.precision, kappa, nullptr, 0, false), c->stream);
+        launch_rescore(L, rescore_args(L, Bs, b, cf.precision, kappa, out, false), c->stream);
     launch_sum_mind(B, b, 0, c->stream);
     HIPCHK(c, hipGetLastError());
-    if (labels_dev)
-        HIPCHK(c, hipMemcpyAsync(labels_dev, B.labels, 4 * (size_t)b, hipMemcpyDeviceToDevice, c->stream));
     // the device scalars and the flags in one read-back
     double io[6];
     HIPCHK(c, hipMemcpyAsync(io, B.obj, sizeof(io), hipMemcpyDeviceToHost, c->stream));

@@ -64,10 +64,10 @@ struct RescoreArgs {
     int split;  // 0: no room, no row is listed
     double *psum;
     RescoreRec *rec;
-    // outputs: the library's arrays, every distance (may be NULL), and the
-    // grouping ranks and counts (rank may be NULL)
-    int32_t *labels;
-    float *mind, *margin;
+    // outputs: the library's arrays, the caller's and every distance (each may
+    // be NULL), and the grouping ranks and counts (rank may be NULL)
+    int32_t *labels, *labels_out;
+    float *mind, *margin, *mind_out, *margin_out;
     double *Dout;
     int64_t ldD;
     int32_t *rank, *gcnt;
@@ -318,6 +318,21 @@ __device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreL
     return true;
 }
 
+// A row's label, distance and margin, to the library's arrays and the caller's.
+template <typename ARGS>
+__device__ __forceinline__ void write_row(const ARGS &A, int row, int label, float mind, float margin)
+{
+    A.labels[row] = label;
+    A.mind[row] = mind;
+    A.margin[row] = margin;
+    if (A.labels_out)
+        A.labels_out[row] = label;
+    if (A.mind_out)
+        A.mind_out[row] = mind;
+    if (A.margin_out)
+        A.margin_out[row] = margin;
+}
+
 // Grouping ranks of one chunk of 64 rows by one wave: the rank of each row
 // among the rows before it with its label, and the chunk's label counts.
 __device__ __forceinline__ void rank_chunk(const RescoreArgs &A, int ch)
@@ -409,9 +424,7 @@ __device__ __forceinline__ bool rescore_listed(const RescoreArgs &A, int nrows)
             if (lane == 0) {
                 const int l = load_agent(&A.labels[row]);
                 const float m = load_agent(&A.mind[row]), g = load_agent(&A.margin[row]);
-                A.labels[row] = l;
-                A.mind[row] = m;
-                A.margin[row] = g;
+                write_row(A, row, l, m, g);
             }
             continue;
         }
@@ -426,9 +439,8 @@ __device__ __forceinline__ bool rescore_listed(const RescoreArgs &A, int nrows)
             R.take(D, j);
         }
         if (lane == 0) {
-            A.labels[row] = R.l < A.k ? R.l : 0;
-            A.mind[row] = (float)R.b;
-            A.margin[row] = (float)(fmin(R.s, load_agent(&A.rec[q].outside)) - R.b);
+            write_row(A, row, R.l < A.k ? R.l : 0, (float)R.b,
+                      (float)(fmin(R.s, load_agent(&A.rec[q].outside)) - R.b));
         }
     }
     __builtin_amdgcn_s_waitcnt(0);
