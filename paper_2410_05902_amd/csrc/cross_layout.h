@@ -31,11 +31,20 @@ inline int direct_rpl(int d, bool fp64) { return !fp64 && d <= 32 ? 2 : 1; }
 
 // Ranges of the direct kernel for nb batch rows: about kDirectWGs workgroups
 // (one round at 8 waves per SIMD), 3/4 of that with two rows per lane (whose
-// registers allow 6 waves per SIMD).
-inline int direct_nranges(int nb, int rpl)
+// registers allow 6 waves per SIMD).  In FP64 a row of 33 to 64 coordinates
+// takes 168 registers, 3 waves per SIMD, one of 17 to 32 takes 106, 4 waves: one
+// round of workgroups that start with long ranges there (b = 1024, M = 4096,
+// d = 64: nine entries per range, behind a start of two load round trips, took
+// 99 us; 22 entries take 63 us).
+inline int direct_nranges(int nb, int d, bool fp64)
 {
+    const int rpl = direct_rpl(d, fp64);
     const int tiles = (nb + 256 * rpl - 1) / (256 * rpl);
-    const int r = (rpl == 2 ? kDirectWGs * 3 / 4 : kDirectWGs) / tiles;
+    const int wgs = rpl == 2                          ? kDirectWGs * 3 / 4
+                    : fp64 && d > 32 && d <= 64       ? kDirectWGs * 3 / 8
+                    : fp64 && d > 16 && d <= 32       ? kDirectWGs / 2
+                                                      : kDirectWGs;
+    const int r = wgs / tiles;
     return r < 1 ? 1 : r;
 }
 

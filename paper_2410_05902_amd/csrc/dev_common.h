@@ -205,6 +205,18 @@ __device__ __forceinline__ int wave_segment_of(const int32_t *__restrict__ off, 
     return lo;
 }
 
+// s / c for s >= 0, correctly rounded, from r = 1 / c correctly rounded: the
+// rounded product and one correction by its exact residual (Markstein), three
+// operations instead of the ten or more of a division.  A product that
+// overflows, or s = inf, gives inf as the division does; NaN stays NaN.
+template <typename T>
+__device__ __forceinline__ T div_by(T s, T c, T r)
+{
+    const T q = s * r;
+    const T e = fma(-q, c, s);
+    return q < (T)INFINITY ? fma(e, r, q) : q;
+}
+
 // ---------------------------------------------------------------------------
 // Gram blocks of one slot, as tasks.  The self-norm of a center held over its
 // support (Section 4.1) is a quadratic form in the blocks
@@ -215,7 +227,9 @@ __device__ __forceinline__ int wave_segment_of(const int32_t *__restrict__ off, 
 //   tasks(j, c) = ceil(na_j / ta) * ceil(ne_jc / te),
 // enumerated over jc = j * C + c with exclusive offsets goff[0 .. k*C].
 // ---------------------------------------------------------------------------
-constexpr int kGramTA = 32;      // slot rows per task of the VALU form
+constexpr int kGramTA = 32;      // slot rows per task of the VALU form in FP32
+// ... in FP64, whose column rows are 64 to a task and each pair 3 times the work
+constexpr int kGramTA64 = 16;
 constexpr int kGramTAMfma = 16;  // ... and of the MFMA form (16 x 16 tiles)
 // Column tiles per task that a plan may choose: 1, 2, ..., 2^(steps - 1).
 // A plan whose tasks outnumber the work kernel's waves takes more tiles per

@@ -33,7 +33,7 @@ __device__ __forceinline__ T kfinish_direct(T s, T cneg, T param)
         if constexpr (sizeof(T) == 4)
             return __builtin_amdgcn_exp2f(s * cneg);  // cneg = -log2(e) / bandwidth
         else
-            return exp(-s / param);
+            return exp(-div_by<T>(s, param, (T)1 / param));
     } else if constexpr (KIND == MBKK_LINEAR) {
         return s;
     } else {
@@ -90,7 +90,7 @@ __device__ __forceinline__ T kval_direct(const T (&x)[DR], const float *__restri
         if constexpr (sizeof(T) == 4)
             return __builtin_amdgcn_exp2f(s * cneg);  // cneg = -log2(e) / bandwidth
         else
-            return exp(-s / param);
+            return exp(-div_by<T>(s, param, (T)1 / param));
     } else if constexpr (KIND == MBKK_LINEAR) {
         return s;
     } else {
@@ -218,7 +218,7 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
                     if constexpr (sizeof(T) == 4)
                         kv = __builtin_amdgcn_exp2f(sacc * cneg);
                     else
-                        kv = exp(-sacc / prm);
+                        kv = exp(-div_by<T>(sacc, prm, (T)1 / prm));
                 } else if constexpr (KIND == MBKK_LINEAR) {
                     kv = sacc;
                 } else {
@@ -274,7 +274,7 @@ static void dispatch_direct_width(const Layout &L, const Buffers &B, int nb, int
 void launch_cross_direct(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64,
                          hipStream_t st)
 {
-    const int nranges = direct_nranges(nb, direct_rpl(L.d, fp64));
+    const int nranges = direct_nranges(nb, L.d, fp64);
     if (fp64) {
         double *P = (double *)B.part;
         switch (kind) {

@@ -43,11 +43,13 @@ __device__ __forceinline__ void gram_term(KT &s, KT x, KT y)
     }
 }
 
+// rprm = 1 / prm, rounded.  (FP64: div_by's correction also holds for the
+// reciprocal of a double.)
 template <int KIND, typename KT>
-__device__ __forceinline__ KT gram_finish(KT s, KT prm)
+__device__ __forceinline__ KT gram_finish(KT s, KT prm, KT rprm)
 {
     if constexpr (KIND == MBKK_GAUSS || KIND == MBKK_LAPLACE)
-        return (KT)exp(-s / prm);
+        return (KT)exp(-div_by<KT>(s, prm, rprm));
     else if constexpr (KIND == MBKK_LINEAR)
         return s;
     else
@@ -55,14 +57,86 @@ __device__ __forceinline__ KT gram_finish(KT s, KT prm)
 }
 
 // VALU tasks: RPL column rows per lane (two in FP32, one in FP64), so a
-// task is 32 slot rows by 64 RPL column rows, and coordinates are held in
-// registers 32 / RPL at a time (the pool stride is a multiple of 32).
+// task is 32 (FP64: 16) slot rows by 64 RPL column rows.
 template <typename KT>
 __host__ __device__ constexpr int gram_valu_rpl()
 {
     return sizeof(KT) == 4 ? 2 : 1;
 }
+template <typename KT>
+__host__ __device__ constexpr int gram_valu_ta()
+{
+    return sizeof(KT) == 4 ? kGramTA : kGramTA64;
+}
 
+// Up to 64 coordinates: the lane's column rows stay in registers (DR >= d
+// coordinates; both rows of a pair are zero past d) and the slot rows come
+// one by one through scalar loads, each coordinate serving the RPL rows, as
+// in the direct cross kernel.  What bounds it is the VALU: 2 operations per
+// coordinate and pair (FP64: also a conversion per coordinate) and the
+// exponential, about 95 instructions a pair at 32 coordinates.  The general
+// kernel below keeps the sums of 32 slot rows in registers instead, which
+// leaves room for 16 coordinates at a time: 890 us against 765 us here for a
+// cluster of 8191 of 8192 rows (32 coordinates, window 4, 2.7e8 pairs), and
+// 28 us against 16 us in FP64 (64 coordinates, k = 50, b = 1024).  Sums over
+// the coordinates run in the same order in both, so the kernel values are the
+// same bits.
+template <int KIND, typename KT, int DR>
+__global__ __launch_bounds__(kGramWG) void k_gram_rows(const GramWork A, int dp, double param,
+                                                       const float *__restrict__ pool32, int zero_row)
+{
+    constexpr int RPL = gram_valu_rpl<KT>(), TA = gram_valu_ta<KT>();
+    const int lane = threadIdx.x & 63;
+    const KT prm = (KT)param, rprm = (KT)1 / prm;
+    __shared__ int32_t stage[kGramStage];
+    gram_wave_loop<64 * RPL, false>(A, stage, blockIdx.x, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int,
+                                                              double &lsum) {
+        bool eok[RPL];
+        KT ev[RPL][DR];
+        const int na = min(TA, a.n - ab * TA);
+        const int ral = (int)gram_row(a, ab * TA + min(lane, na - 1));
+#pragma unroll
+        for (int q = 0; q < RPL; ++q) {
+            const int qe = eb * 64 * RPL + q * 64 + lane;
+            eok[q] = qe < ec.n;
+            const float *pe = pool32 + (int64_t)(int)gram_row(ec, min(qe, ec.n - 1)) * dp;
+#pragma unroll
+            for (int u = 0; u < DR; u += 4) {
+                const f32x4 v = *(const f32x4 *)(pe + u);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    ev[q][u + t] = (KT)v[t];
+            }
+        }
+        double sum[RPL];
+#pragma unroll
+        for (int q = 0; q < RPL; ++q)
+            sum[q] = 0.0;
+        for (int i = 0; i < na; ++i) {  // wave uniform
+            const float *pa = pool32 + (int64_t)__builtin_amdgcn_readlane(ral, i) * dp;
+            KT acc[RPL];
+#pragma unroll
+            for (int q = 0; q < RPL; ++q)
+                acc[q] = 0;
+#pragma unroll
+            for (int u = 0; u < DR; ++u) {
+                const KT au = (KT)pa[u];
+#pragma unroll
+                for (int q = 0; q < RPL; ++q)
+                    gram_term<KIND, KT>(acc[q], au, ev[q][u]);
+            }
+#pragma unroll
+            for (int q = 0; q < RPL; ++q)
+                sum[q] += (double)gram_finish<KIND, KT>(acc[q], prm, rprm);
+        }
+#pragma unroll
+        for (int q = 0; q < RPL; ++q)
+            lsum += eok[q] ? sum[q] : 0.0;
+    });
+}
+
+// More than 64 coordinates: coordinates are held in
+// registers 32 / RPL at a time (the pool stride is a multiple of 32).
 // Column rows eb*64 RPL + 64 q + l (q < RPL) of lane l are held in registers,
 // 32 / RPL coordinates at a time; the task's slot rows are read with
 // wave-uniform addresses and each coordinate serves the RPL rows.  Pairs,
@@ -71,10 +145,10 @@ template <int KIND, typename KT>
 __global__ __launch_bounds__(kGramWG) void k_gram_valu(const GramWork A, int d, int dp, double param,
                                                        const float *__restrict__ pool32, int zero_row)
 {
-    constexpr int RPL = gram_valu_rpl<KT>();
+    constexpr int RPL = gram_valu_rpl<KT>(), TA = gram_valu_ta<KT>();
     constexpr int DC = 32 / RPL;
     const int lane = threadIdx.x & 63;
-    const KT prm = (KT)param;
+    const KT prm = (KT)param, rprm = (KT)1 / prm;
     __shared__ int32_t stage[kGramStage];
     // (one column set per task: the VALU plan takes Q = 1)
     gram_wave_loop<64 * RPL, false>(A, stage, blockIdx.x, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int,
@@ -87,13 +161,13 @@ __global__ __launch_bounds__(kGramWG) void k_gram_valu(const GramWork A, int d, 
             eok[q] = qe < ec.n;
             re[q] = eok[q] ? (int)gram_row(ec, qe) : zero_row;
         }
-        const int na = min(kGramTA, a.n - ab * kGramTA);
-        const int ral = lane < na ? (int)gram_row(a, ab * kGramTA + lane) : zero_row;
-        KT acc[RPL][kGramTA];
+        const int na = min(TA, a.n - ab * TA);
+        const int ral = lane < na ? (int)gram_row(a, ab * TA + lane) : zero_row;
+        KT acc[RPL][TA];
 #pragma unroll
         for (int q = 0; q < RPL; ++q)
 #pragma unroll
-            for (int i = 0; i < kGramTA; ++i)
+            for (int i = 0; i < TA; ++i)
                 acc[q][i] = 0;
         for (int t0 = 0; t0 < d; t0 += DC) {
             KT ev[RPL][DC];
@@ -110,7 +184,7 @@ __global__ __launch_bounds__(kGramWG) void k_gram_valu(const GramWork A, int d, 
                 }
             }
 #pragma unroll
-            for (int i = 0; i < kGramTA; ++i) {
+            for (int i = 0; i < TA; ++i) {
                 if (i < na) {  // wave uniform
                     const int ra = __builtin_amdgcn_readlane(ral, i);
                     const float *pa = pool32 + (int64_t)ra * dp + t0;
@@ -128,9 +202,9 @@ __global__ __launch_bounds__(kGramWG) void k_gram_valu(const GramWork A, int d, 
         for (int q = 0; q < RPL; ++q) {
             if (eok[q]) {
 #pragma unroll
-                for (int i = 0; i < kGramTA; ++i)
+                for (int i = 0; i < TA; ++i)
                     if (i < na)
-                        lsum += (double)gram_finish<KIND, KT>(acc[q][i], prm);
+                        lsum += (double)gram_finish<KIND, KT>(acc[q][i], prm, rprm);
             }
         }
     });
@@ -185,7 +259,7 @@ int gram_task_cols(int mfma, int fp64)
     return mfma ? 16 : 64 * (fp64 ? gram_valu_rpl<double>() : gram_valu_rpl<float>());
 }
 
-int gram_task_rows(int mfma) { return mfma ? kGramTAMfma : kGramTA; }
+int gram_task_rows(int mfma, int fp64) { return mfma ? kGramTAMfma : (fp64 ? kGramTA64 : kGramTA); }
 // the MFMA task loads its 16 slot rows once for up to MBKK_GRAM_QMAX column
 // tiles (a power of two, at most 2^(kGramTileSteps - 1)); the VALU task
 // takes one column set
@@ -207,8 +281,21 @@ static void launch_gram_valu(const Layout &L, const Buffers &B, const GramWork &
 {
     const dim3 grid(kGramWaves / (kGramWG / 64));
     const int zr = (int)L.PR;
-#define MBKK_GV(K) \
-    hipLaunchKernelGGL((k_gram_valu<K, KT>), grid, dim3(kGramWG), 0, st, A, L.d, L.dp, param, B.pool32, zr)
+#define MBKK_GVR(K, DR) \
+    hipLaunchKernelGGL((k_gram_rows<K, KT, DR>), grid, dim3(kGramWG), 0, st, A, L.dp, param, B.pool32, zr)
+#define MBKK_GV(K)                                                                                                  \
+    do {                                                                                                            \
+        if (L.d <= 8)                                                                                               \
+            MBKK_GVR(K, 8);                                                                                         \
+        else if (L.d <= 16)                                                                                         \
+            MBKK_GVR(K, 16);                                                                                        \
+        else if (L.d <= 32)                                                                                         \
+            MBKK_GVR(K, 32);                                                                                        \
+        else if (L.d <= 64)                                                                                         \
+            MBKK_GVR(K, 64);                                                                                        \
+        else                                                                                                        \
+            hipLaunchKernelGGL((k_gram_valu<K, KT>), grid, dim3(kGramWG), 0, st, A, L.d, L.dp, param, B.pool32, zr); \
+    } while (0)
     switch (kind) {
     case MBKK_GAUSS: MBKK_GV(MBKK_GAUSS); break;
     case MBKK_LAPLACE: MBKK_GV(MBKK_LAPLACE); break;
@@ -216,6 +303,7 @@ static void launch_gram_valu(const Layout &L, const Buffers &B, const GramWork &
     default: MBKK_GV(MBKK_POLY2); break;
     }
 #undef MBKK_GV
+#undef MBKK_GVR
 }
 
 static void launch_gram_mfma(const Layout &L, const Buffers &B, const GramWork &A, double kappa, hipStream_t st)
