@@ -302,20 +302,24 @@ void launch_cross_direct(const Layout &L, const Buffers &B, int nb, int kind, do
 // weighted sum over the support is then an in-lane reduction plus one
 // exchange between the two lane halves.
 //
-// Workgroup tile: 128 support rows x 128 batch rows, 4 waves in a 2x2 grid,
-// each wave 64 x 64 = 2 x 2 MFMA blocks of 32 x 32; K staged through LDS in
-// chunks of 32 (one LDS buffer, next chunk prefetched into registers).  Segments are padded to multiples of 32
-// rows so that every 32-row block belongs to one center.  Output: one partial
-// per (32-row block, batch row); the two blocks of a wave are merged when they
-// belong to the same center.
+// Workgroup tile: 128 support rows x 64 batch rows, 4 waves in a 2x2 grid,
+// each wave 64 x 32 = 2 MFMA blocks of 32 x 32; K staged through LDS in chunks
+// of 32 (one LDS buffer, next chunk prefetched into registers), four
+// workgroups per compute unit.  What bounds it is the matrix core, and the
+// last round of tiles: with 128 x 128 tiles, two workgroups per unit, b = 1024
+// rows against 8192 entries are 536 tiles for 512 places, and the second round
+// held 24 of them (164 us in FP32 at 784 coordinates; 115 us with these
+// tiles, which are half a round's worth each).  Segments are padded to
+// multiples of 32 rows so that every 32-row block belongs to one center.
+// Output: one partial per (32-row block, batch row); the two blocks of a wave
+// are merged when they belong to the same center.
 //   MODE 0: FP32 MFMA 32x32x2 (plain form)
 //   MODE 1: BF16 32x32x16, hi.hi + hi.lo + lo.hi (compensated split)
 //   MODE 2: BF16 32x32x16, hi.hi only
 // ===========================================================================
 
 struct CrossArgs {
-    int nb, dp, ntB;
-    int64_t ntiles;           // support tiles * batch tiles
+    int nb, dp, ntB;          // ntB: batch tiles
     int64_t zero_row;
     const int32_t *seg_total; // seg_off + k: used support rows
     const float *pool32;
@@ -333,39 +337,39 @@ struct CrossArgs {
     int ldp;
 };
 
-constexpr int TS = 128, TB = 128, KC = 32;
+constexpr int TS = 128, TB = 64, KC = 32;
 constexpr int LDF = KC + 4;  // FP32 LDS row stride (floats): 144 B, conflict-free b128 reads
 constexpr int LDH = KC + 8;  // BF16 LDS row stride (elements): 80 B
 
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void k_cross_mfma(const CrossArgs A)
+__global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
 {
     constexpr bool F32 = MODE == 0;
     constexpr bool X3 = MODE == 1;
     // LDS (one buffer; the next K chunk is prefetched into registers):
     // FP32 -> As, Bs [TS][LDF] floats; BF16 -> hi (and lo) [TS][LDH] each
-    constexpr int LDS_F = F32 ? 2 * TS * LDF : 4;
-    constexpr int LDS_H = F32 ? 8 : TS * LDH;
+    constexpr int LDS_F = F32 ? (TS + TB) * LDF : 4;
+    constexpr int LDS_A = F32 ? 8 : TS * LDH, LDS_B = F32 ? 8 : TB * LDH;
     __shared__ __attribute__((aligned(16))) float smf[LDS_F];
-    __shared__ __attribute__((aligned(16))) uint16_t sAh[LDS_H];
-    __shared__ __attribute__((aligned(16))) uint16_t sAl[X3 ? LDS_H : 8];
-    __shared__ __attribute__((aligned(16))) uint16_t sBh[LDS_H];
-    __shared__ __attribute__((aligned(16))) uint16_t sBl[X3 ? LDS_H : 8];
+    __shared__ __attribute__((aligned(16))) uint16_t sAh[LDS_A];
+    __shared__ __attribute__((aligned(16))) uint16_t sAl[X3 ? LDS_A : 8];
+    __shared__ __attribute__((aligned(16))) uint16_t sBh[LDS_B];
+    __shared__ __attribute__((aligned(16))) uint16_t sBl[X3 ? LDS_B : 8];
     __shared__ __attribute__((aligned(16))) float sAy[TS];
     __shared__ __attribute__((aligned(16))) float sW[TS];
 
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int wm = wid >> 1, wn = wid & 1;
-    // XCD-aware tile order: consecutive tiles of one XCD share support rows
-    const int64_t G8 = gridDim.x / 8;
-    const int64_t t = (int64_t)(blockIdx.x % 8) * G8 + blockIdx.x / 8;
-    if (t >= A.ntiles)
+    // XCD-aware tile order: the tiles of the support as it is, cut into eight
+    // contiguous shares, so that consecutive tiles of one XCD share support
+    // rows and a support smaller than its capacity still spreads over all XCDs
+    const int M = *A.seg_total;
+    const int64_t ntiles = (int64_t)((M + TS - 1) / TS) * A.ntB, share = (ntiles + 7) / 8;
+    const int64_t t = (int64_t)(blockIdx.x % 8) * share + blockIdx.x / 8;
+    if (blockIdx.x / 8 >= share || t >= ntiles)
         return;
     const int st = (int)(t / A.ntB), bt = (int)(t % A.ntB);
-    const int M = *A.seg_total;
     const int s0 = st * TS, b0 = bt * TB;
-    if (s0 >= M)
-        return;
 
     // per-tile support row metadata
     if (tid < TS) {
@@ -376,46 +380,49 @@ __global__ __launch_bounds__(256, 2) void k_cross_mfma(const CrossArgs A)
     }
 
     const int nK = A.dp / KC;
-    f32x16 acc[2][2];
+    f32x16 acc[2];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int bb = 0; bb < 2; ++bb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                acc[a][bb][i] = 0.0f;
+        for (int i = 0; i < 16; ++i)
+            acc[a][i] = 0.0f;
 
     if constexpr (F32) {
-        // loader: 4 rows per thread, one float4 each, for A and B
+        // loader: 4 rows of A and 2 of B per thread, one float4 each
         const int lr = tid >> 3, lc = (tid & 7) * 4;
         const float *asrc[4];
-        const float *bsrc[4];
-        bool bok[4];
+        const float *bsrc[2];
+        bool bok[2];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int r = lr + 32 * q;
-            const int s = s0 + r;
+            const int s = s0 + lr + 32 * q;
             const int64_t prow = s < M ? (int64_t)A.sup_row[s] : A.zero_row;
             asrc[q] = A.pool32 + prow * A.dp + lc;
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int r = lr + 32 * q;
             bok[q] = b0 + r < A.nb;
             bsrc[q] = A.bat32 + (int64_t)(bok[q] ? b0 + r : 0) * A.dp + lc;
         }
-        f32x4 ra[4], rb[4];
+        f32x4 ra[4], rb[2];
         auto gload = [&](int kc) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 4; ++q)
                 ra[q] = *(const f32x4 *)(asrc[q] + kc * KC);
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
                 rb[q] = bok[q] ? *(const f32x4 *)(bsrc[q] + kc * KC) : f32x4{0, 0, 0, 0};
-            }
         };
         auto lstore = [&]() {
             float *As = smf;
             float *Bs = As + TS * LDF;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 4; ++q)
                 *(f32x4 *)(As + (lr + 32 * q) * LDF + lc) = ra[q];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
                 *(f32x4 *)(Bs + (lr + 32 * q) * LDF + lc) = rb[q];
-            }
         };
         gload(0);
         lstore();
@@ -427,25 +434,21 @@ __global__ __launch_bounds__(256, 2) void k_cross_mfma(const CrossArgs A)
             const float *As = smf;
             const float *Bs = As + TS * LDF;
             // K permutation inside the chunk: MFMA step s, lane half h -> column h*16 + s
-            f32x4 af[2][4], bf[2][4];
+            f32x4 af[2][4], bf[4];
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     af[a][v] = *(const f32x4 *)(As + (wm * 64 + a * 32 + frow) * LDF + fh * 16 + v * 4);
 #pragma unroll
-            for (int bb = 0; bb < 2; ++bb)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    bf[bb][v] = *(const f32x4 *)(Bs + (wn * 64 + bb * 32 + frow) * LDF + fh * 16 + v * 4);
+            for (int v = 0; v < 4; ++v)
+                bf[v] = *(const f32x4 *)(Bs + (wn * 32 + frow) * LDF + fh * 16 + v * 4);
 #pragma unroll
             for (int s = 0; s < 16; ++s)
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int bb = 0; bb < 2; ++bb)
-                        acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[a][s >> 2][s & 3], bf[bb][s >> 2][s & 3],
-                                                                           acc[a][bb], 0, 0, 0);
+                    acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[a][s >> 2][s & 3], bf[s >> 2][s & 3], acc[a], 0, 0,
+                                                                  0);
             if (kc + 1 < nK) {
                 __syncthreads();
                 lstore();
@@ -453,46 +456,43 @@ __global__ __launch_bounds__(256, 2) void k_cross_mfma(const CrossArgs A)
             }
         }
     } else {
-        // loader: 2 rows per thread, 8 bf16 (16 B) each, hi and lo, for A and B
+        // loader: 2 rows of A and one of B per thread, 8 bf16 (16 B) each, hi and lo
         const int lr = tid >> 2, lc = (tid & 3) * 8;
-        const uint16_t *ahs[2], *als[2], *bhs[2], *bls[2];
-        bool bok[2];
+        const uint16_t *ahs[2], *als[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int r = lr + 64 * q;
-            const int s = s0 + r;
+            const int s = s0 + lr + 64 * q;
             const int64_t prow = s < M ? (int64_t)A.sup_row[s] : A.zero_row;
             ahs[q] = A.poolhi + prow * A.dp + lc;
             als[q] = A.poollo + prow * A.dp + lc;
-            bok[q] = b0 + r < A.nb;
-            const int64_t brow = bok[q] ? b0 + r : 0;
-            bhs[q] = A.bathi + brow * A.dp + lc;
-            bls[q] = A.batlo + brow * A.dp + lc;
         }
-        u16x8 rah[2], ral[2], rbh[2], rbl[2];
+        const bool bok = b0 + lr < A.nb;
+        const int64_t brow = bok ? b0 + lr : 0;
+        const uint16_t *bhs = A.bathi + brow * A.dp + lc, *bls = A.batlo + brow * A.dp + lc;
+        u16x8 rah[2], ral[2], rbh, rbl;
         const u16x8 z8 = {0, 0, 0, 0, 0, 0, 0, 0};
         auto gload = [&](int kc) {
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 rah[q] = *(const u16x8 *)(ahs[q] + kc * KC);
-                rbh[q] = bok[q] ? *(const u16x8 *)(bhs[q] + kc * KC) : z8;
-                if constexpr (X3) {
+                if constexpr (X3)
                     ral[q] = *(const u16x8 *)(als[q] + kc * KC);
-                    rbl[q] = bok[q] ? *(const u16x8 *)(bls[q] + kc * KC) : z8;
-                }
             }
+            rbh = bok ? *(const u16x8 *)(bhs + kc * KC) : z8;
+            if constexpr (X3)
+                rbl = bok ? *(const u16x8 *)(bls + kc * KC) : z8;
         };
         auto lstore = [&]() {
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int off = (lr + 64 * q) * LDH + lc;
                 *(u16x8 *)(sAh + off) = rah[q];
-                *(u16x8 *)(sBh + off) = rbh[q];
-                if constexpr (X3) {
+                if constexpr (X3)
                     *(u16x8 *)(sAl + off) = ral[q];
-                    *(u16x8 *)(sBl + off) = rbl[q];
-                }
             }
+            *(u16x8 *)(sBh + lr * LDH + lc) = rbh;
+            if constexpr (X3)
+                *(u16x8 *)(sBl + lr * LDH + lc) = rbl;
         };
         gload(0);
         lstore();
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(256, 2) void k_cross_mfma(const CrossArgs A)
                 gload(kc + 1);
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                bf16x8 ah[2], al[2], bh[2], bl[2];
+                bf16x8 ah[2], al[2], bh, bl;
 #pragma unroll
                 for (int a = 0; a < 2; ++a) {
                     const int off = (wm * 64 + a * 32 + frow) * LDH + s * 16 + fh * 8;
@@ -511,23 +511,18 @@ __global__ __launch_bounds__(256, 2) void k_cross_mfma(const CrossArgs A)
                     if constexpr (X3)
                         al[a] = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sAl + off));
                 }
+                const int boff = (wn * 32 + frow) * LDH + s * 16 + fh * 8;
+                bh = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sBh + boff));
+                if constexpr (X3)
+                    bl = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sBl + boff));
 #pragma unroll
-                for (int bb = 0; bb < 2; ++bb) {
-                    const int off = (wn * 64 + bb * 32 + frow) * LDH + s * 16 + fh * 8;
-                    bh[bb] = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sBh + off));
-                    if constexpr (X3)
-                        bl[bb] = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sBl + off));
-                }
-#pragma unroll
-                for (int a = 0; a < 2; ++a)
-#pragma unroll
-                    for (int bb = 0; bb < 2; ++bb) {
-                        acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[bb], acc[a][bb], 0, 0, 0);
-                        if constexpr (X3) {
-                            acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[bb], acc[a][bb], 0, 0, 0);
-                            acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[bb], acc[a][bb], 0, 0, 0);
-                        }
+                for (int a = 0; a < 2; ++a) {
+                    acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh, acc[a], 0, 0, 0);
+                    if constexpr (X3) {
+                        acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl, acc[a], 0, 0, 0);
+                        acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh, acc[a], 0, 0, 0);
                     }
+                }
             }
             if (kc + 1 < nK) {
                 __syncthreads();
@@ -541,48 +536,39 @@ __global__ __launch_bounds__(256, 2) void k_cross_mfma(const CrossArgs A)
     // and support rows m = 8 (i / 4) + 4 (l / 32) + i % 4, i = 0..15.
     const int n = lane & 31, h = lane >> 5;
     const int Mb = M / 32;
-    float tot[2][2];
+    float tot[2];
+    const int col = b0 + wn * 32 + n;
+    const float ax = col < A.nb ? A.c1 * A.batsq[col] : 0.0f;
 #pragma unroll
-    for (int bb = 0; bb < 2; ++bb) {
-        const int col = b0 + wn * 64 + bb * 32 + n;
-        const float ax = col < A.nb ? A.c1 * A.batsq[col] : 0.0f;
+    for (int a = 0; a < 2; ++a) {
+        const int mbase = wm * 64 + a * 32;
+        float sum = 0.0f;
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            const int mbase = wm * 64 + a * 32;
-            float sum = 0.0f;
+        for (int g = 0; g < 4; ++g) {
+            const int m0 = mbase + 8 * g + 4 * h;
+            const f32x4 ay = *(const f32x4 *)(sAy + m0);
+            const f32x4 w = *(const f32x4 *)(sW + m0);
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int m0 = mbase + 8 * g + 4 * h;
-                const f32x4 ay = *(const f32x4 *)(sAy + m0);
-                const f32x4 w = *(const f32x4 *)(sW + m0);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float arg = fmaf(acc[a][bb][4 * g + q], A.c2, ax + ay[q]);
-                    sum = fmaf(w[q], __builtin_amdgcn_exp2f(arg), sum);
-                }
+            for (int q = 0; q < 4; ++q) {
+                const float arg = fmaf(acc[a][4 * g + q], A.c2, ax + ay[q]);
+                sum = fmaf(w[q], __builtin_amdgcn_exp2f(arg), sum);
             }
-            sum += __shfl_xor(sum, 32);
-            tot[a][bb] = sum;
         }
+        sum += __shfl_xor(sum, 32);
+        tot[a] = sum;
     }
     const int blk0 = (s0 + wm * 64) / 32;
     if (blk0 >= Mb)
         return;
     const bool has1 = blk0 + 1 < Mb;
     const bool merge = has1 && A.blk_center[blk0] == A.blk_center[blk0 + 1];
-    if (h == 0) {
-#pragma unroll
-        for (int bb = 0; bb < 2; ++bb) {
-            const int col = b0 + wn * 64 + bb * 32 + n;
-            if (col >= A.nb)
-                continue;
-            if (merge) {
-                A.part[(int64_t)blk0 * A.ldp + col] = tot[0][bb] + tot[1][bb];
-            } else {
-                A.part[(int64_t)blk0 * A.ldp + col] = tot[0][bb];
-                if (has1)
-                    A.part[(int64_t)(blk0 + 1) * A.ldp + col] = tot[1][bb];
-            }
+    if (h == 0 && col < A.nb) {
+        if (merge) {
+            A.part[(int64_t)blk0 * A.ldp + col] = tot[0] + tot[1];
+        } else {
+            A.part[(int64_t)blk0 * A.ldp + col] = tot[0];
+            if (has1)
+                A.part[(int64_t)(blk0 + 1) * A.ldp + col] = tot[1];
         }
     }
 }
@@ -1229,8 +1215,7 @@ void launch_cross_mfma(const Layout &L, const Buffers &B, int nb, int precision,
     A.nb = nb;
     A.dp = L.dp;
     A.ntB = (nb + TB - 1) / TB;
-    const int64_t ntS = L.Mcap / TS;
-    A.ntiles = ntS * A.ntB;
+    const int64_t ntiles = L.Mcap / TS * A.ntB;  // of a full support
     A.zero_row = L.PR;
     A.seg_total = B.seg_off + L.k;
     A.pool32 = B.pool32;
@@ -1248,7 +1233,7 @@ void launch_cross_mfma(const Layout &L, const Buffers &B, int nb, int precision,
     A.c1 = (float)(-l2e / kappa);
     A.part = (float *)B.part;
     A.ldp = L.bmax;
-    const int64_t grid = (A.ntiles + 7) / 8 * 8;
+    const int64_t grid = (ntiles + 7) / 8 * 8;
     if (precision == MBKK_FP32)
         hipLaunchKernelGGL(k_cross_mfma<0>, dim3((unsigned)grid), dim3(256), 0, st, A);
     else if (precision == MBKK_BF16X3)
