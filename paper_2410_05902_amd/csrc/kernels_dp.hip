@@ -516,9 +516,10 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
     constexpr int NE = kDpMfmaStage;
     constexpr int NTH = 64 * 8 / NBX;       // threads of a workgroup (256 points)
     constexpr int TPE = NTH / kDpMfmaStage; // staging threads per entry
-    constexpr int UPT = NE * DP * ES / NTH / 16;  // 16-byte pieces per array staged per thread and stage
+    constexpr int PPR = DP * ES / 16;       // 16-byte pieces of a row
+    constexpr int UPT = (PPR + TPE - 1) / TPE;    // ... per array staged per thread and stage, at most
     constexpr int NARR = X3 ? 2 : 1;
-    static_assert(UPT >= 1 && (X3 || KS % 4 == 0), "staging in 16-byte pieces");
+    static_assert(DP * ES % 16 == 0 && (X3 || KS % 4 == 0), "staging in 16-byte pieces");
     typedef typename std::conditional<X3, uint16_t, float>::type elem_t;
     __shared__ __attribute__((aligned(16))) elem_t sY[2][NARR][NE * RS];
     __shared__ __attribute__((aligned(16))) float sAy[2][NE];
@@ -567,8 +568,8 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
         hx[q] = -0.5f * ss;
     }
     // ---- staging of grouped entries [e0, e0 + 64) into buffer bb ------------
-    // thread t stages entry t / TPE, 16-byte pieces (t % TPE) * UPT .. + UPT of its
-    // row in every array (FP32 row, or the BF16 hi and lo rows)
+    // thread t stages entry t / TPE, the 16-byte pieces t % TPE, t % TPE + TPE, ...
+    // of its row in every array (FP32 row, or the BF16 hi and lo rows)
     const int se = tid / TPE, sq = tid % TPE;
     f32x4 pre[NARR][UPT];
     float pay = 0.0f;
@@ -582,7 +583,8 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
                                  : (const char *)(pool32 + r0);
 #pragma unroll
             for (int u = 0; u < UPT; ++u)
-                pre[a][u] = row < 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : *(const f32x4 *)(src + (sq * UPT + u) * 16);
+                pre[a][u] = row < 0 || u * TPE + sq >= PPR ? f32x4{0.f, 0.f, 0.f, 0.f}
+                                                           : *(const f32x4 *)(src + (u * TPE + sq) * 16);
         }
         pay = row < 0 ? 0.0f : ayc * poolsq[row];
     };
@@ -596,7 +598,8 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
             char *dst = (char *)&sY[bb][a][srow * RS];
 #pragma unroll
             for (int u = 0; u < UPT; ++u)
-                *(f32x4 *)(dst + (sq * UPT + u) * 16) = pre[a][u];
+                if (u * TPE + sq < PPR)
+                    *(f32x4 *)(dst + (u * TPE + sq) * 16) = pre[a][u];
         }
         if (sq == 0)
             sAy[bb][srow] = pay;
