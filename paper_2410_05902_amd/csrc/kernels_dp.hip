@@ -491,7 +491,9 @@ __global__ __launch_bounds__(kDpTableWG) void k_dp_table(int64_t n, int d, int64
 // the two lane halves are combined (permlane32 swap) and
 //     S[j][x] = (alpha_j / b_j) sum_{y in B^j} K(x, y)
 // is stored; k_dp_blend then forms T <- (1 - alpha) T + S for the touched
-// centers.  Entries past the support are zero rows outside every segment.
+// centers (200 us at 1M points, k = 100; reading T here at every segment's end
+// or start made the waves wait for it, 900 us).  Entries past the support are
+// zero rows outside every segment.
 // ---------------------------------------------------------------------------
 constexpr int kDpMfmaStage = 64;  // grouped entries per LDS stage
 
@@ -506,7 +508,7 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
                                                     const float *__restrict__ poolsq, int k,
                                                     const int32_t *__restrict__ seg,
                                                     const int32_t *__restrict__ sup_row,
-                                                    const double *__restrict__ wgt, float c2,
+                                                    const double *__restrict__ wgt, float c2, int init,
                                                     float *__restrict__ S, int64_t ldT)
 {
     constexpr int HD = DP / 2;              // coordinates per lane half
@@ -534,20 +536,40 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
     const int64_t x0 = (int64_t)blockIdx.x * 256 + w * (32 * NBX);
     typedef typename std::conditional<X3, bf16x8, float>::type bfrag_t;
     bfrag_t bxh[NBX][KS], bxl[NBX][X3 ? KS : 1];
-    float hx[NBX];
+    // a lane's half row: 16-byte loads, all in flight, where every one lies
+    // inside the row and is aligned (else up to 64 loads of 4 bytes, each under a
+    // condition of its own)
+    const bool whole = d == DP && ld % 4 == 0 && ((uintptr_t)X & 15) == 0;
+    auto load_row = [&](const float *xr, f32x4 (&xv)[HD / 4]) {
+        if (whole) {  // launch uniform
+#pragma unroll
+            for (int i = 0; i < HD / 4; ++i)
+                xv[i] = *(const f32x4 *)(xr + h * HD + 4 * i);
+        } else {
+#pragma unroll
+            for (int i = 0; i < HD / 4; ++i)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int t = h * HD + 4 * i + u;
+                    xv[i][u] = t < d ? xr[t] : 0.0f;
+                }
+        }
+    };
+    f32x16 hx[NBX];  // -|x|^2 / 2 in every element: the accumulator a tile starts from
 #pragma unroll
     for (int q = 0; q < NBX; ++q) {
         const int64_t row = x0 + q * 32 + nn;
         const float *xr = X + (row < n ? row : 0) * ld;
         float ss = 0.0f;
         if constexpr (X3) {
+            f32x4 xv[2 * KS];
+            load_row(xr, xv);
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
                 u16x8 vh, vl;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const int t = h * HD + 8 * s + u;
-                    const float v = t < d ? xr[t] : 0.0f;
+                    const float v = xv[2 * s + u / 4][u % 4];
                     ss = fmaf(v, v, ss);
                     const uint16_t hb = f32_to_bf16_rne(v);
                     vh[u] = hb;
@@ -557,25 +579,32 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
                 bxl[q][s] = __builtin_bit_cast(bf16x8, vl);
             }
         } else {
+            f32x4 xv[KS / 4];
+            load_row(xr, xv);
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                const int t = h * HD + s;
-                bxh[q][s] = t < d ? xr[t] : 0.0f;
+                bxh[q][s] = xv[s / 4][s % 4];
                 ss = fmaf(bxh[q][s], bxh[q][s], ss);
             }
         }
         ss += __shfl_xor(ss, 32);
-        hx[q] = -0.5f * ss;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            hx[q][i] = -0.5f * ss;
     }
     // ---- staging of grouped entries [e0, e0 + 64) into buffer bb ------------
     // thread t stages entry t / TPE, the 16-byte pieces t % TPE, t % TPE + TPE, ...
     // of its row in every array (FP32 row, or the BF16 hi and lo rows)
     const int se = tid / TPE, sq = tid % TPE;
+    // (the pool row of the thread's entry in the next stage to fetch is loaded a
+    // stage before: fetching by a row still in flight held every wave at the
+    // start of every stage)
     f32x4 pre[NARR][UPT];
     float pay = 0.0f;
+    int frow;
+    auto fetch_row = [&](int e0) { frow = sup_row[min(e0 + se, M - 1)]; };
     auto fetch = [&](int e0) {
-        const int e = e0 + se;
-        const int row = e < M ? sup_row[e] : -1;
+        const int row = e0 + se < M ? frow : -1;
         const int64_t r0 = (int64_t)(row < 0 ? 0 : row) * DP;
 #pragma unroll
         for (int a = 0; a < NARR; ++a) {
@@ -605,75 +634,288 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
             sAy[bb][srow] = pay;
     };
     // ---- segment bookkeeping (wave uniform) ---------------------------------
-    // The current center j, the end of its segment and its weight are held in
-    // registers, loaded when j becomes current (a segment usually spans
-    // tiles), so that the epilogue does not wait on memory.
-    int j = wave_segment_of(seg, k, 0);
-    int cur_end = seg[j + 1];
-    float cur_w = (float)wgt[j];
+    // Lane l holds center jb + l: the end of its segment and its weight.  The
+    // current center's are read from the lanes: as scalar loads at every
+    // segment's end (about one per tile at 41 entries a center) they were two
+    // waits on memory in each wave's in-order stream.
+    int jb = 0, w_end;
+    float w_wgt;
+    auto window = [&](int base) {
+        jb = base;
+        const int jl = min(jb + lane, k - 1);
+        w_end = seg[jl + 1];
+        w_wgt = (float)wgt[jl];
+    };
+    int j, cur_end;
+    float cur_w;
+    const int64_t col = NBX == 2 ? x0 + h * 32 + nn : x0 + nn;  // the lane's point in a store
+    const bool cok = col < n && (NBX == 2 || h == 0);
+    // makes the first center whose segment ends after `end` current (there is one)
+    auto advance = [&](int end) {
+        uint64_t m;
+        while ((m = __ballot(jb + lane < k && w_end > end)) == 0)
+            window(jb + 64);
+        const int l = __ffsll((unsigned long long)m) - 1;
+        j = jb + l;
+        cur_end = __builtin_amdgcn_readlane(w_end, l);
+        cur_w = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_wgt), l));
+    };
+    // end of the segment after the one that ends at `end` (M if there is none):
+    // from the window; a segment whose successor lies beyond it is taken for
+    // one followed by more
+    auto next_end = [&](int end) -> int {
+        if (end >= M)
+            return M;
+        const uint64_t m = __ballot(jb + lane < k && w_end > end);
+        return m ? __builtin_amdgcn_readlane(w_end, __ffsll((unsigned long long)m) - 1) : 0;
+    };
+    // the segment that ends at `end` (in the window)
+    auto segment_of_end = [&](int end, int &jj, float &ww) {
+        const int l = __ffsll((unsigned long long)__ballot(jb + lane < k && w_end >= end)) - 1;
+        jj = jb + l;
+        ww = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w_wgt), l));
+    };
+    window(0);
+    advance(0);
     float run[NBX];
 #pragma unroll
     for (int q = 0; q < NBX; ++q)
         run[q] = 0.0f;
-    auto store = [&]() {
-        if constexpr (NBX == 2) {
-            const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(run[0]), __float_as_uint(run[1]),
-                                                             false, false);
-            const float tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-            const int64_t col = x0 + h * 32 + nn;  // lanes < 32: block 0, lanes >= 32: block 1
-            if (col < n)
-                S[(int64_t)j * ldT + col] = cur_w * tot;
+    auto store = [&](const float (&r)[NBX]) {
+        float tot;
+        if constexpr (NBX == 2) {  // lanes < 32: block 0, lanes >= 32: block 1
+            const auto sw =
+                __builtin_amdgcn_permlane32_swap(__float_as_uint(r[0]), __float_as_uint(r[1]), false, false);
+            tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
         } else {
-            const float tot = run[0] + __shfl_xor(run[0], 32);
-            const int64_t col = x0 + nn;
-            if (h == 0 && col < n)
-                S[(int64_t)j * ldT + col] = cur_w * tot;
+            tot = r[0] + __shfl_xor(r[0], 32);
         }
-#pragma unroll
-        for (int q = 0; q < NBX; ++q)
-            run[q] = 0.0f;
+        if (cok)
+            S[(int64_t)j * ldT + col] = cur_w * tot;
     };
-    // segment sums of a tile of kernel values (entries [t0, t0 + 32))
+    // Segment sums of a tile of kernel values (entries [t0, t0 + 32)).  Element
+    // i of lane half h is entry 16 h + i.  Three forms, by the tile's segment
+    // ends (wave uniform): none inside, so no masks; one, at which the sums so
+    // far move to `fin` and start again, in one lane half between two elements
+    // and in the other before its first or after its last; several, in one pass
+    // as well.  (Masking each segment's elements took about 6 instructions for
+    // each element and segment.)  Masks are left where the support ends, or the
+    // tile's segments are spread over more than the window's centers.
     auto segments = [&](const f32x16 (&kv)[NBX], int t0) {
-        int lo = t0;
         const int top = min(t0 + 32, M);
+        if (init) {
+            // one entry per center, in center order, and weight 1: the kernel
+            // values are the table's
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int e = t0 + 16 * h + i;
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    if (e < top && x0 + q * 32 + nn < n)
+                        S[(int64_t)e * ldT + x0 + q * 32 + nn] = kv[q][i];
+            }
+            return;
+        }
+        if (cur_end >= t0 + 32) {  // the whole tile in one segment
+#pragma unroll
+            for (int q = 0; q < NBX; ++q) {
+                float sq_ = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    sq_ += kv[q][i];
+                run[q] += sq_;
+            }
+            if (cur_end == t0 + 32) {
+                store(run);
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    run[q] = 0.0f;
+                if (cur_end < M)
+                    advance(cur_end);
+            }
+            return;
+        }
+        const int nx = next_end(cur_end);  // end of the following segment (M if there is none)
+        if (top == t0 + 32 && nx >= top) {
+            const int m = cur_end - t0;           // 1 .. 31: the tile's entries below m finish the segment
+            const int mi = m <= 16 ? m : m - 16;  // where the split lane half splits, 1 .. 16
+            const bool sp = (h == 0) == (m <= 16);  // lanes of that half
+            float fin[NBX];
+#pragma unroll
+            for (int q = 0; q < NBX; ++q) {
+                // m <= 16: lane half 1 lies wholly in the next segment
+                fin[q] = run[q];
+                run[q] = m <= 16 && !sp ? 0.0f : run[q];
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (i == mi) {  // wave uniform
+#pragma unroll
+                    for (int q = 0; q < NBX; ++q) {
+                        fin[q] = sp ? run[q] : fin[q];
+                        run[q] = sp ? 0.0f : run[q];
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    run[q] += kv[q][i];
+            }
+#pragma unroll
+            for (int q = 0; q < NBX; ++q) {
+                // m > 16: lane half 0 lies wholly in the segment that ended
+                if (m > 16 || mi == 16) {  // wave uniform
+                    const bool end0 = m > 16 ? !sp : sp;
+                    fin[q] = end0 ? run[q] : fin[q];
+                    run[q] = end0 ? 0.0f : run[q];
+                }
+            }
+            store(fin);
+            advance(cur_end);
+            if (cur_end == top) {
+                store(run);
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    run[q] = 0.0f;
+                if (cur_end < M)
+                    advance(cur_end);
+            }
+            return;
+        }
+        // more than one segment end inside (or the support's end): bit e of
+        // `ends` marks a segment that ends before entry t0 + e
+        uint32_t ends = 0;
+        bool seen = true;  // every one of them lies in the window
+        for (int e = cur_end; e < top;) {
+            ends |= 1u << (e - t0);
+            e = next_end(e);
+            if (e == 0) {
+                seen = false;
+                break;
+            }
+        }
+        if (seen && top == t0 + 32) {
+            // One pass over the elements; a lane half whose segment ends puts
+            // its sum aside.  A segment that lies in one half is stored from
+            // there; the first one (with sums from earlier tiles in both
+            // halves) and the one that runs from half 0 into half 1 are
+            // combined over the halves.
+            const int e1 = __ffs((int)ends) - 1;  // the current segment's end, 1 .. 31
+            const uint32_t m0 = ends & 0xffffu, m1 = ends >> 16;  // before element i of half 0 / 1
+            // half 1's sums of the current segment where it ends in half 0, and of
+            // the one that runs over entry 16 where it ends in half 1
+            float fin[NBX], crs[NBX];
+#pragma unroll
+            for (int q = 0; q < NBX; ++q) {
+                fin[q] = crs[q] = run[q];
+                run[q] = e1 <= 16 && h == 1 ? 0.0f : run[q];
+            }
+            bool first = true;       // the current segment has not been stored
+            bool cross = !(m1 & 1);  // a segment runs over entry 16 into half 1
+            int cj = 0;              // that segment, once it has ended
+            float cw = 0.0f;
+            auto put = [&](int e, const float (&r)[NBX], bool mine) {  // half `mine` holds the whole sum
+                int jj;
+                float ww;
+                segment_of_end(t0 + e, jj, ww);
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    if (mine && x0 + q * 32 + nn < n)
+                        S[(int64_t)jj * ldT + x0 + q * 32 + nn] = ww * (r[q] + 0.0f);
+            };
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (i > 0 && ((m0 >> i) & 1)) {  // wave uniform: a segment ends in half 0
+                    if (first) {
+                        float r[NBX];
+#pragma unroll
+                        for (int q = 0; q < NBX; ++q)
+                            r[q] = h == 0 ? run[q] : fin[q];
+                        store(r);
+                        first = false;
+                    } else {
+                        put(i, run, h == 0);
+                    }
+#pragma unroll
+                    for (int q = 0; q < NBX; ++q)
+                        run[q] = h == 0 ? 0.0f : run[q];
+                }
+                if (i > 0 && ((m1 >> i) & 1)) {  // ... in half 1
+                    if (cross) {
+                        cross = false;
+#pragma unroll
+                        for (int q = 0; q < NBX; ++q)
+                            crs[q] = run[q];
+                        segment_of_end(t0 + 16 + i, cj, cw);
+                        cj += 1;  // (0: none)
+                    } else {
+                        put(16 + i, run, h == 1);
+                    }
+#pragma unroll
+                    for (int q = 0; q < NBX; ++q)
+                        run[q] = h == 1 ? 0.0f : run[q];
+                }
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    run[q] += kv[q][i];
+            }
+            if (m1 & 1) {  // half 0's last segment ends at its end
+                if (first) {
+                    float r[NBX];
+#pragma unroll
+                    for (int q = 0; q < NBX; ++q)
+                        r[q] = h == 0 ? run[q] : fin[q];
+                    store(r);
+                } else {
+                    put(16, run, h == 0);
+                }
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    run[q] = h == 0 ? 0.0f : run[q];
+            } else if (cj > 0) {  // the segment over entry 16 has ended in half 1
+                float r[NBX];
+#pragma unroll
+                for (int q = 0; q < NBX; ++q) {
+                    r[q] = h == 0 ? run[q] : crs[q];
+                    run[q] = h == 0 ? 0.0f : run[q];
+                }
+                j = cj - 1;
+                cur_w = cw;
+                store(r);
+            }
+            // the segment that goes on
+            advance(t0 + 31 - __clz((int)ends));
+            if (cur_end == top) {
+                store(run);
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    run[q] = 0.0f;
+                if (cur_end < M)
+                    advance(cur_end);
+            }
+            return;
+        }
+        int lo = t0;
         while (lo < top) {  // wave uniform
             const int end = cur_end;
             const int hi = min(end, top);
             const int mlo = lo - t0, mhi = hi - t0;
-            if (mlo == 0 && mhi == 32) {  // the whole tile in one segment: no masks
+            // the segment's elements are [a_h, b_h) with wave-uniform bounds per half
+            const int a0 = min(max(mlo, 0), 16), b0 = min(max(mhi, 0), 16);
+            const int a1 = min(max(mlo - 16, 0), 16), b1 = min(max(mhi - 16, 0), 16);
 #pragma unroll
-                for (int q = 0; q < NBX; ++q) {
-                    float sq_ = 0.0f;
+            for (int i = 0; i < 16; ++i) {
+                const bool in = h == 0 ? (i >= a0 && i < b0) : (i >= a1 && i < b1);
 #pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        sq_ += kv[q][i];
-                    run[q] += sq_;
-                }
-            } else {
-                // element i of lane half h is entry 16 h + i: the segment's
-                // elements are [a_h, b_h) with wave-uniform bounds per half
-                const int a0 = min(max(mlo, 0), 16), b0 = min(max(mhi, 0), 16);
-                const int a1 = min(max(mlo - 16, 0), 16), b1 = min(max(mhi - 16, 0), 16);
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const bool in = h == 0 ? (i >= a0 && i < b0) : (i >= a1 && i < b1);
-#pragma unroll
-                    for (int q = 0; q < NBX; ++q)
-                        run[q] += in ? kv[q][i] : 0.0f;
-                }
+                for (int q = 0; q < NBX; ++q)
+                    run[q] += in ? kv[q][i] : 0.0f;
             }
             if (end <= top) {
-                store();
-                if (end < M) {
-                    int e1;
-                    do {
-                        ++j;
-                        e1 = seg[j + 1];
-                    } while (e1 <= end);
-                    cur_end = e1;
-                    cur_w = (float)wgt[j];
-                }
+                store(run);
+#pragma unroll
+                for (int q = 0; q < NBX; ++q)
+                    run[q] = 0.0f;
+                if (end < M)
+                    advance(end);
             }
             lo = hi;
         }
@@ -709,11 +951,6 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
         }
     };
     auto tile = [&](f32x16 (&accN)[NBX], f32x16 (&accP)[NBX], int bb, int t32) {
-#pragma unroll
-        for (int q = 0; q < NBX; ++q)
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                accN[q][i] = hx[q];
         if constexpr (X3) {
             const uint16_t *arh = &sY[bb][0][(t32 * 32 + nn) * RS + h * HD];
             const uint16_t *arl = &sY[bb][1][(t32 * 32 + nn) * RS + h * HD];
@@ -734,7 +971,8 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
                     for (int q = 0; q < NBX; ++q) {
                         const bf16x8 aa = pr == 2 ? al : ah;
                         const bf16x8 bv = pr == 1 ? bxl[q][s] : bxh[q][s];
-                        accN[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aa, bv, accN[q], 0, 0, 0);
+                        accN[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aa, bv, s == 0 && pr == 0 ? hx[q] : accN[q],
+                                                                          0, 0, 0);
                         exp_share(accP, (s * 3 + pr) * NBX + q);
                     }
                 ah = ahn;
@@ -751,7 +989,8 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
                 for (int u = 0; u < 4; ++u)
 #pragma unroll
                     for (int q = 0; q < NBX; ++q) {
-                        accN[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u], bxh[q][s4 + u], accN[q], 0, 0, 0);
+                        accN[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u], bxh[q][s4 + u],
+                                                                       s4 + u == 0 ? hx[q] : accN[q], 0, 0, 0);
                     }
                 av = an;
             }
@@ -764,8 +1003,10 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
             for (int mi = 0; mi < NMF; ++mi)
                 exp_share(accP, mi);
         }
+        __builtin_amdgcn_s_setprio(3);
         if (prev >= 0)
             segments(accP, prev);
+        __builtin_amdgcn_s_setprio(0);
         // the new tile's exponent constants, for its epilogue during the next tile
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -776,14 +1017,18 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
         }
     };
     const int nst = (M + NE - 1) / NE;
+    fetch_row(0);
     fetch(0);
+    fetch_row(NE);
     commit(0);
     __syncthreads();
     static_assert(NE == 64, "two tiles per stage: the tile parity selects the accumulator set");
     for (int st = 0; st < nst; ++st) {
         const int bb = st & 1;
-        if (st + 1 < nst)
+        if (st + 1 < nst) {
             fetch((st + 1) * NE);
+            fetch_row((st + 2) * NE);
+        }
         tile(accA, accB, bb, 0);
         prev = st * NE;
         if (st * NE + 32 < M) {  // wave uniform
@@ -808,12 +1053,12 @@ __global__ __launch_bounds__(NBX == 2 ? 256 : 512, 2) void k_dp_mfma(int64_t n, 
     }
 }
 
-// T[j][x] <- (1 - alpha_j) T[j][x] + S[j][x] for the centers with batch points
-// (init: T <- S).  A thread owns 4 consecutive points and runs over the
-// centers, skipping (wave uniform) those the batch did not touch.
+// T[j][x] <- (1 - alpha_j) T[j][x] + S[j][x] for the centers with batch points.
+// A thread owns 4 consecutive points and runs over the centers, skipping
+// (wave uniform) those the batch did not touch.
 __global__ __launch_bounds__(256) void k_dp_blend(int64_t n, int k, const int32_t *__restrict__ seg,
                                                   const double *__restrict__ alpha, const float *__restrict__ S,
-                                                  float *__restrict__ T, int64_t ldT, int init)
+                                                  float *__restrict__ T, int64_t ldT)
 {
     const int64_t x = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (x >= n)
@@ -823,17 +1068,13 @@ __global__ __launch_bounds__(256) void k_dp_blend(int64_t n, int k, const int32_
             continue;
         const f32x4 sv = *(const f32x4 *)(S + (int64_t)j * ldT + x);
         f32x4 *tp = (f32x4 *)(T + (int64_t)j * ldT + x);  // ldT is a multiple of 64: whole vectors
-        if (init) {
-            *tp = sv;
-        } else {
-            const float keep = (float)(1.0 - alpha[j]);
-            const f32x4 tv = *tp;
-            f32x4 r;
+        const float keep = (float)(1.0 - alpha[j]);
+        const f32x4 tv = *tp;
+        f32x4 r;
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                r[u] = fmaf(keep, tv[u], sv[u]);
-            *tp = r;
-        }
+        for (int u = 0; u < 4; ++u)
+            r[u] = fmaf(keep, tv[u], sv[u]);
+        *tp = r;
     }
 }
 
@@ -844,7 +1085,8 @@ static void launch_dp_mfma(const Layout &L, const Buffers &B, const int32_t *seg
     const dim3 grid((unsigned)((L.n + 255) / 256));
 #define MBKK_DP_MFMA(DPV, X3, NBX)                                                                                \
     hipLaunchKernelGGL((k_dp_mfma<DPV, X3, NBX>), grid, dim3(NBX == 2 ? 256 : 512), 0, st, L.n, L.d, B.ld, B.X,    \
-                       B.pool32, B.poolhi, B.poollo, B.poolsq, L.k, seg, sup_row, B.dp_w, c2, B.dp_S, L.ldT)
+                       B.pool32, B.poolhi, B.poollo, B.poolsq, L.k, seg, sup_row, B.dp_w, c2, init,                \
+                       init ? (float *)B.dp_T : B.dp_S, L.ldT)
 #define MBKK_DP_MFMA_W(X3)                     \
     switch (L.dp) {                             \
     case 32: MBKK_DP_MFMA(32, X3, 2); break;    \
@@ -859,8 +1101,10 @@ static void launch_dp_mfma(const Layout &L, const Buffers &B, const int32_t *seg
     }
 #undef MBKK_DP_MFMA_W
 #undef MBKK_DP_MFMA
+    if (init)
+        return;
     hipLaunchKernelGGL(k_dp_blend, dim3((unsigned)((L.n + 1023) / 1024)), dim3(256), 0, st, L.n, L.k, seg, B.alpha,
-                       B.dp_S, (float *)B.dp_T, L.ldT, init);
+                       B.dp_S, (float *)B.dp_T, L.ldT);
 }
 
 // Rows per lane of the table update: two for FP32 rows of at most 32
