@@ -40,7 +40,7 @@ namespace mbkk {
 constexpr int kDpScoreWaves = 16;  // waves of a scoring workgroup; lane = row, waves split the centers
 constexpr int kDpTableWG = 256;
 constexpr int kDpTile = 64;         // rows and columns of a pair task
-constexpr int kDpGramWGs = 1024;    // workgroups of the pair-task kernel (4 waves each, tasks grid-strided)
+constexpr int kDpGramWGs = 2048;    // workgroups of the pair-task kernel (a task each, grid-strided)
 
 // Kernel value from the coordinate reduction s (squared distance, L1 distance
 // or dot product) and the parameter.
@@ -243,36 +243,55 @@ __global__ __launch_bounds__(1024) void k_dp_plan(int k, int b, int lr, const in
 // entry (batch row r lives in pool row row0 + r), its center and its old
 // table value.
 // ---------------------------------------------------------------------------
+// A workgroup takes kDpGroupRows rows, four threads to a row: each counts a
+// quarter of the rows before it, four labels per LDS read.  (A thread counting
+// all of them one by one took 58 us at b = 4096, the last row's 4096 reads; 23 us
+// so.)
+constexpr int kDpGroupRows = 64;
+
 template <typename TT>
 __global__ __launch_bounds__(256) void k_dp_group(int b, const int32_t *__restrict__ labels,
                                                   const int32_t *__restrict__ seg, const TT *__restrict__ tsel,
                                                   int64_t row0, int32_t *__restrict__ sup_row,
                                                   int32_t *__restrict__ gctr, TT *__restrict__ gsel)
 {
-    __shared__ int lab[kMaxBatch];
-    for (int q = threadIdx.x; q < b; q += 256)
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) int lab[kMaxBatch];
+    const int r0 = blockIdx.x * kDpGroupRows, top = min(b, r0 + kDpGroupRows);
+    for (int q = threadIdx.x; q < top; q += 256)
         lab[q] = labels[q];
     __syncthreads();
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r >= b)
-        return;
-    const int l = lab[r];
+    const int r = r0 + (threadIdx.x >> 2), part = threadIdx.x & 3;
+    const int l = r < b ? lab[r] : -1;
     int before = 0;
-    for (int q = 0; q < r; ++q)
-        before += lab[q] == l;
-    const int pos = seg[l] + before;
-    sup_row[pos] = (int32_t)(row0 + r);
-    gctr[pos] = l;
-    gsel[pos] = tsel[r];
+    const int quads = r < b ? r / 4 : 0;  // whole groups of four rows before r
+    for (int g = part; g < quads; g += 4) {
+        const i32x4 v = *(const i32x4 *)&lab[4 * g];
+        before += (v[0] == l) + (v[1] == l) + (v[2] == l) + (v[3] == l);
+    }
+    const int rest = 4 * quads + part;
+    if (r < b && rest < r)
+        before += lab[rest] == l;
+    before += __shfl_xor(before, 1);
+    before += __shfl_xor(before, 2);
+    if (r < b && part == 0) {
+        const int pos = seg[l] + before;
+        sup_row[pos] = (int32_t)(row0 + r);
+        gctr[pos] = l;
+        gsel[pos] = tsel[r];
+    }
 }
 
 // ---------------------------------------------------------------------------
 // Pair sums of the grouped batch.  Center j's pairs are cut into tiles of 64
 // rows by 64 columns (nt_j^2 tasks, nt_j = ceil(b_j / 64), offsets toff from
-// the plan); a wave takes one task at a time: lane = row (coordinates in
-// registers), the columns broadcast one by one as in the table update.  The
-// tile's row sums (kernel values in the table type, summed over at most 64
-// columns) go to pp[column tile][row] in FP64.
+// the plan); a workgroup takes one task at a time: lane = row (coordinates in
+// registers), each of its four waves a quarter of the columns, broadcast one by
+// one as in the table update.  The tile's row sums (kernel values in the table
+// type, summed over at most 16 columns, then the four sums in FP64) go to
+// pp[column tile][row].  With balanced clusters there are few tasks (k = 100,
+// b = 4096: about 150), so one task's length counts: one wave with all 64
+// columns took 104 us at 128 coordinates, 33 us so.
 // ---------------------------------------------------------------------------
 template <int KIND, typename TT, int DR>
 __global__ __launch_bounds__(256) void k_dp_gram(int k, int bmax, int dp, const float *__restrict__ pool32,
@@ -280,11 +299,12 @@ __global__ __launch_bounds__(256) void k_dp_gram(int k, int bmax, int dp, const 
                                                  const int32_t *__restrict__ seg, const int32_t *__restrict__ toff,
                                                  double param, double *__restrict__ pp)
 {
+    __shared__ double part[4][kDpTile];
     const int lane = threadIdx.x & 63;
-    const int nw = gridDim.x * 4;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int T = toff[k];
     const TT cneg = (TT)(-1.4426950408889634 / param), prm = (TT)param;
-    for (int task = blockIdx.x * 4 + (threadIdx.x >> 6); task < T; task += nw) {  // wave uniform
+    for (int task = blockIdx.x; task < T; task += gridDim.x) {  // workgroup uniform
         const int j = wave_segment_of(toff, k, task);
         const int s0 = seg[j], bj = seg[j + 1] - s0;
         const int nt = (bj + kDpTile - 1) / kDpTile;
@@ -297,9 +317,9 @@ __global__ __launch_bounds__(256) void k_dp_gram(int k, int bmax, int dp, const 
 #pragma unroll
         for (int t = 0; t < DR; ++t)
             x[t] = (TT)xr[t];
-        const int c0 = s0 + ct * kDpTile;
-        const int cn = min(kDpTile, s0 + bj - c0);
-        const int lrow = sup_row[c0 + (lane < cn ? lane : 0)];
+        const int c0 = s0 + ct * kDpTile + w * (kDpTile / 4);  // the wave's columns
+        const int cn = min(kDpTile / 4, s0 + bj - c0);
+        const int lrow = sup_row[lane < cn ? c0 + lane : s0];
         TT acc = 0;
         for (int q = 0; q < cn; ++q) {  // wave uniform
             const float *__restrict__ y = pool32 + (int64_t)__builtin_amdgcn_readlane(lrow, q) * dp;
@@ -309,8 +329,11 @@ __global__ __launch_bounds__(256) void k_dp_gram(int k, int bmax, int dp, const 
                 a = dp_kstep<KIND, TT>(x[t], (TT)y[t], a);
             acc += dp_kfinish<KIND, TT>(a, cneg, prm);
         }
-        if (act)
-            pp[(int64_t)ct * bmax + e] = (double)acc;
+        part[w][lane] = (double)acc;
+        __syncthreads();
+        if (w == 0 && act)
+            pp[(int64_t)ct * bmax + e] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+        __syncthreads();
     }
 }
 
@@ -1249,7 +1272,7 @@ static void dp_update_t(const Layout &L, const Buffers &B, int b, int kind, doub
                        B.dp_toff);
     const dim3 gb((unsigned)((b + 255) / 256));
     const int64_t row0 = slot_row(L, 0, 0);
-    hipLaunchKernelGGL(k_dp_group<TT>, gb, dim3(256), 0, st, b, B.labels, B.seg_off, (const TT *)B.dp_tsel, row0,
+    hipLaunchKernelGGL(k_dp_group<TT>, dim3((unsigned)((b + kDpGroupRows - 1) / kDpGroupRows)), dim3(256), 0, st, b, B.labels, B.seg_off, (const TT *)B.dp_tsel, row0,
                        B.sup_row, B.dp_gctr, (TT *)B.dp_gsel);
     switch (kind) {
     case MBKK_GAUSS: dp_gram_kind<MBKK_GAUSS, TT>(L, B, param, st); break;
