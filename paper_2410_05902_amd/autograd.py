@@ -23,7 +23,8 @@ class BatchObjective(torch.autograd.Function):
         ctx.sigma = s
         ctx.sig_meta = (sigma.dtype, sigma.device)
         ctx.save_for_backward(xb.detach(), labels)
-        return torch.tensor(f, dtype=torch.float64, device=xb.device)
+        # (a fill by value: torch.tensor would copy from pageable host memory)
+        return torch.full((), f, dtype=torch.float64, device=xb.device)
 
     @staticmethod
     def backward(ctx, grad_f: torch.Tensor):

@@ -17,6 +17,8 @@ struct RowOutputs {
 
 // p[0 .. nwords) = v (32-bit words): the library's only way of clearing memory.
 void launch_fill32(void *p, uint32_t v, int64_t nwords, hipStream_t st);
+// n 32-bit words (at most 64) from the workspace to pinned host memory.
+void launch_report(const void *src, void *dst_host, int n, hipStream_t st);
 void launch_row_sqnorm(const float *X, int64_t n, int d, int64_t ld, float *sqn, unsigned int *sqmax,
                        hipStream_t st);
 // frag_mode 1 / 2: also write the rows (as batch rows 0..cnt-1) in MFMA

@@ -32,6 +32,17 @@ void launch_fill32(void *p, uint32_t v, int64_t nwords, hipStream_t st)
     hipLaunchKernelGGL(k_fill32, dim3((unsigned)blocks), dim3(256), 0, st, (uint32_t *)p, v, nwords);
 }
 
+__global__ __launch_bounds__(64) void k_report(const uint32_t *__restrict__ src, uint32_t *dst_host, int n)
+{
+    if ((int)threadIdx.x < n)
+        __hip_atomic_store(&dst_host[threadIdx.x], src[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+void launch_report(const void *src, void *dst_host, int n, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, st, (const uint32_t *)src, (uint32_t *)dst_host, n);
+}
+
 // ---------------------------------------------------------------------------
 // ||x||^2 for every row of X, summed in FP64, stored as FP32 (data norms),
 // and their maximum over the finite ones (as FP32 bits in *sqmax, which the

@@ -50,6 +50,10 @@ struct mbkk_ctx {
     size_t ev_used = 0;
     double ms_acc = 0.0;
     int64_t launches = 0;
+    // pinned host copy of the device scalars and flags, written by the device
+    // (NULL: read back by a copy; always so with a static workspace, which
+    // allocates nothing)
+    void *mail = nullptr;
     std::string err;
 };
 
@@ -349,15 +353,26 @@ static int take_fold(mbkk_ctx *c, uint32_t *mask)
     return rr;
 }
 
-static int check_flags(mbkk_ctx *c)
+// The device scalars and error flags (adjacent in the workspace).
+struct Scalars {
+    double obj[4];
+    int32_t flags[4];
+};
+
+// Waits for the stream and reads them.  One read serves a call's objective and
+// its checks; the device writes them to pinned memory (a copy to pageable
+// memory, and a second one for the flags, were half of a small call's time).
+static int read_scalars(mbkk_ctx *c, Scalars *s)
 {
-    int32_t f[2] = {0, 0};
-    HIPCHK(c, hipMemcpyAsync(f, c->B.flags, sizeof(f), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (f[0])
-        return fail(c, MBKK_E_INDEX, "index outside [0, n)");
-    if (f[1])
-        return fail(c, MBKK_E_NONFINITE, "non-finite value in a gathered row");
+    if (c->mail) {
+        launch_report(c->B.obj, c->mail, sizeof(Scalars) / 4, c->stream);
+        HIPCHK(c, hipGetLastError());
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        memcpy(s, c->mail, sizeof(Scalars));
+    } else {
+        HIPCHK(c, hipMemcpyAsync(s, c->B.obj, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+    }
     return MBKK_OK;
 }
 
@@ -366,6 +381,40 @@ static int clear_flags(mbkk_ctx *c)
     launch_fill32(c->B.flags, 0, 4, c->stream);
     HIPCHK(c, hipGetLastError());
     return MBKK_OK;
+}
+
+// The flags are 0 between calls: who reads a raised one clears them.
+static int report_flags(mbkk_ctx *c, const Scalars &s)
+{
+    if (!s.flags[0] && !s.flags[1])
+        return MBKK_OK;
+    int rc = clear_flags(c);
+    if (rc)
+        return rc;
+    return s.flags[0] ? fail(c, MBKK_E_INDEX, "index outside [0, n)")
+                      : fail(c, MBKK_E_NONFINITE, "non-finite value in a gathered row");
+}
+
+static int check_flags(mbkk_ctx *c)
+{
+    Scalars s;
+    int rc = read_scalars(c, &s);
+    return rc ? rc : report_flags(c, s);
+}
+
+// The end of a call that may return an objective (scalar `which` over `rows`
+// rows) and, under validate, checks the flags.
+static int finish(mbkk_ctx *c, double *f_host, int which, int64_t rows)
+{
+    if (!f_host && !c->cfg.validate)
+        return MBKK_OK;
+    Scalars s;
+    int rc = read_scalars(c, &s);
+    if (rc)
+        return rc;
+    if (f_host)
+        *f_host = s.obj[which] / (double)rows;
+    return c->cfg.validate ? report_flags(c, s) : MBKK_OK;
 }
 
 // A positive tie_delta replaces the per-row error bound of the BF16 forms.
@@ -622,6 +671,8 @@ int mbkk_destroy(mbkk_ctx *c)
         c->device = -1;
         return MBKK_OK;
     }
+    if (c->mail)
+        (void)hipHostFree(c->mail);
     delete c;
     return MBKK_OK;
 }
@@ -642,6 +693,12 @@ int mbkk_set_data(mbkk_ctx *c, const float *X, int64_t ld)
     unsigned int bits = 0;
     HIPCHK(c, hipMemcpyAsync(&bits, c->B.sqmax, sizeof(bits), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    // (here, where the stream is waited for anyway: a call that may be captured
+    // allocates nothing)
+    if (c->device < 0 && !c->mail && hipHostMalloc(&c->mail, sizeof(Scalars), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+        (void)hipGetLastError();
+        c->mail = nullptr;
+    }
     float f;
     memcpy(&f, &bits, sizeof(f));
     c->ymax2 = (double)f;
@@ -655,8 +712,6 @@ static int init_common(mbkk_ctx *c, const int32_t *idx_dev)
 {
     const Layout &L = c->L;
     Buffers &B = c->B;
-    if (c->cfg.validate && clear_flags(c))
-        return MBKK_E_HIP;
     // pool rows [0, k) <- X[idx]
     launch_gather_rows(B.X, L.n, L.d, B.ld, idx_dev, L.k, L.dp, B.pool32, L.bf16 ? B.poolhi : nullptr,
                        L.bf16 ? B.poollo : nullptr, B.poolsq, B.poolsq64, B.init_idx, B.flags, c->cfg.validate,
@@ -726,8 +781,6 @@ static int dp_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels
     const Layout &L = c->L;
     Buffers &B = c->B;
     const mbkk_config &cf = c->cfg;
-    if (cf.validate && clear_flags(c))
-        return MBKK_E_HIP;
     set_batch_view(c, 0);
     launch_gather_rows(B.X, L.n, L.d, B.ld, batch, b, L.dp, B.bat32, B.bathi, B.batlo, B.batsq, B.batsq64, B.batidx,
                        B.flags, cf.validate, c->stream);
@@ -753,15 +806,7 @@ static int dp_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels
     c->slot_b[0] = b;
     c->iter += 1;
     c->version++;
-    if (fbefore_host) {
-        double s = 0.0;
-        HIPCHK(c, hipMemcpyAsync(&s, B.obj + 1, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        *fbefore_host = s / (double)b;
-    }
-    if (cf.validate)
-        return check_flags(c);
-    return MBKK_OK;
+    return finish(c, fbefore_host, 1, b);
 }
 
 int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev, float *mind_dev,
@@ -779,8 +824,6 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
     Buffers &B = c->B;
     const int64_t i = c->iter;
     const int W = L.W;
-    if (c->cfg.validate && clear_flags(c))
-        return MBKK_E_HIP;
     prepare(c, batch, b);
     RowOutputs out;
     out.labels = labels_dev;
@@ -816,15 +859,7 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
     c->slot_b[p_new] = b;
     c->iter = i + 1;
     c->version++;
-    if (fbefore_host) {
-        double s = 0.0;
-        HIPCHK(c, hipMemcpyAsync(&s, B.obj, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        *fbefore_host = s / (double)b;
-    }
-    if (c->cfg.validate)
-        return check_flags(c);
-    return MBKK_OK;
+    return finish(c, fbefore_host, 0, b);
 }
 
 int mbkk_assign(mbkk_ctx *c, const int32_t *idx, int64_t m, int32_t *labels_dev, float *mind_dev,
@@ -838,8 +873,6 @@ int mbkk_assign(mbkk_ctx *c, const int32_t *idx, int64_t m, int32_t *labels_dev,
         return fail(c, MBKK_E_INVALID, "bad index array");
     const Layout &L = c->L;
     Buffers &B = c->B;
-    if (c->cfg.validate && clear_flags(c))
-        return MBKK_E_HIP;
     if (m == 0 && !L.untrunc)
         prepare(c, nullptr, 0);
     for (int64_t m0 = 0; m0 < m; m0 += L.bmax) {
@@ -873,8 +906,6 @@ int mbkk_objective(mbkk_ctx *c, const int32_t *idx, int64_t m, double *out_host)
     if (m <= 0 || !idx || !out_host)
         return fail(c, MBKK_E_INVALID, "need m > 0 indices and an output");
     const Layout &L = c->L;
-    if (c->cfg.validate && clear_flags(c))
-        return MBKK_E_HIP;
     for (int64_t m0 = 0; m0 < m; m0 += L.bmax) {
         const int nb = (int)((m - m0) < L.bmax ? (m - m0) : L.bmax);
         if (L.untrunc) {
@@ -888,13 +919,7 @@ int mbkk_objective(mbkk_ctx *c, const int32_t *idx, int64_t m, double *out_host)
         }
         launch_sum_mind(c->B, nb, m0 > 0, c->stream);
     }
-    double s = 0.0;
-    HIPCHK(c, hipMemcpyAsync(&s, c->B.obj + 1, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    *out_host = s / (double)m;
-    if (c->cfg.validate)
-        return check_flags(c);
-    return MBKK_OK;
+    return finish(c, out_host, 1, m);
 }
 
 int mbkk_last_batch_objective(mbkk_ctx *c, double *f_host)
@@ -966,7 +991,6 @@ int mbkk_agreement(mbkk_ctx *c, const int32_t *labels_dev, const int32_t *truth_
     const int k = c->L.k;
     if (nc < 1 || (int64_t)k * nc > ((int64_t)1 << 26))
         return fail(c, MBKK_E_INVALID, "need 1 <= c and k * c <= 2^26");
-    launch_fill32(c->B.flags, 0, 4, c->stream);
     launch_fill32(table_dev, 0, 2 * (int64_t)k * nc, c->stream);
     launch_contingency(labels_dev, truth_dev, m, k, nc, table_dev, c->B.flags, c->stream);
     HIPCHK(c, hipGetLastError());
@@ -975,8 +999,10 @@ int mbkk_agreement(mbkk_ctx *c, const int32_t *labels_dev, const int32_t *truth_
     HIPCHK(c, hipMemcpyAsync(n.data(), table_dev, sizeof(int64_t) * n.size(), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipMemcpyAsync(f, c->B.flags, sizeof(f), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    if (f[2])
-        return fail(c, MBKK_E_INVALID, "label outside [0, k) or truth outside [0, c)");
+    if (f[2]) {
+        int rc = clear_flags(c);
+        return rc ? rc : fail(c, MBKK_E_INVALID, "label outside [0, k) or truth outside [0, c)");
+    }
     agreement_scores(n, k, nc, ari_host, nmi_host);
     return MBKK_OK;
 }
@@ -1042,8 +1068,6 @@ int mbkk_objective_fwd(mbkk_ctx *c, const float *xb_dev, int32_t b, double sigma
     Buffers &B = c->B;
     const mbkk_config &cf = c->cfg;
     const double kappa = 2.0 * sigma * sigma;
-    if (clear_flags(c))
-        return MBKK_E_HIP;
     // the rows go to the free slot of the current iteration
     set_batch_view(c, phys_of(c->iter, L.P));
     launch_gather_rows(xb_dev, b, L.d, L.d, nullptr, b, L.dp, B.bat32, B.bathi, B.batlo, B.batsq, B.batsq64, nullptr,
@@ -1075,16 +1099,16 @@ int mbkk_objective_fwd(mbkk_ctx *c, const float *xb_dev, int32_t b, double sigma
         launch_rescore(L, rescore_args(L, Bs, b, cf.precision, kappa, out, false), c->stream);
     launch_sum_mind(B, b, 0, c->stream);
     HIPCHK(c, hipGetLastError());
-    // the device scalars and the flags in one read-back
-    double io[6];
-    HIPCHK(c, hipMemcpyAsync(io, B.obj, sizeof(io), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    int32_t f[4];
-    memcpy(f, io + 4, sizeof(f));
-    if (f[1])
-        return fail(c, MBKK_E_NONFINITE, "non-finite value in the coordinates");
+    Scalars s;
+    rc = read_scalars(c, &s);
+    if (rc)
+        return rc;
+    if (s.flags[1]) {
+        rc = clear_flags(c);
+        return rc ? rc : fail(c, MBKK_E_NONFINITE, "non-finite value in the coordinates");
+    }
     if (f_host)
-        *f_host = io[1] / (double)b;
+        *f_host = s.obj[1] / (double)b;
     return MBKK_OK;
 }
 
@@ -1102,8 +1126,6 @@ int mbkk_objective_bwd(mbkk_ctx *c, const float *xb_dev, int32_t b, double sigma
         return fail(c, MBKK_E_INVALID, "g must be finite");
     const Layout &L = c->L;
     Buffers &B = c->B;
-    if (clear_flags(c))
-        return MBKK_E_HIP;
     // the support layout and the self norms of a forward at this state and
     // sigma are still valid; otherwise they are made here
     if (c->layout_version != c->version)
@@ -1119,14 +1141,15 @@ int mbkk_objective_bwd(mbkk_ctx *c, const float *xb_dev, int32_t b, double sigma
         launch_grad_rows(L, B, xb_dev, b, sigma, labels_dev, g, B.dNsig, dX_dev, B.rowds, B.obj + 2, c->stream);
     }
     HIPCHK(c, hipGetLastError());
-    double io[6];
-    HIPCHK(c, hipMemcpyAsync(io, B.obj, sizeof(io), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    int32_t f[4];
-    memcpy(f, io + 4, sizeof(f));
-    if (f[2])
-        return fail(c, MBKK_E_INVALID, "label outside [0, k)");
-    *dsigma_host = io[2];
+    Scalars s;
+    rc = read_scalars(c, &s);
+    if (rc)
+        return rc;
+    if (s.flags[2]) {
+        rc = clear_flags(c);
+        return rc ? rc : fail(c, MBKK_E_INVALID, "label outside [0, k)");
+    }
+    *dsigma_host = s.obj[2];
     return MBKK_OK;
 }
 
