@@ -227,10 +227,18 @@ __device__ __forceinline__ T div_by(T s, T c, T r)
 //   tasks(j, c) = ceil(na_j / ta) * ceil(ne_jc / te),
 // enumerated over jc = j * C + c with exclusive offsets goff[0 .. k*C].
 // ---------------------------------------------------------------------------
-constexpr int kGramTA = 32;      // slot rows per task of the VALU form in FP32
-// ... in FP64, whose column rows are 64 to a task and each pair 3 times the work
-constexpr int kGramTA64 = 16;
-constexpr int kGramTAMfma = 16;  // ... and of the MFMA form (16 x 16 tiles)
+// Slot rows per task: of the VALU form in FP32 and FP64 (whose column rows are
+// 64 to a task and each pair 3 times the work) with rows of up to 64
+// coordinates ...
+constexpr int kGramTA = 32, kGramTA64 = 16;
+// ... and of rows of at most 8 coordinates, where loading a task's column rows
+// again is cheap and there are few tasks (2-D blobs, b = 256, k = 3: 45 tasks of
+// 32 rows took 13 us, 6.6 us so; b = 2048, k = 50: 16.8 -> 10.4; 16 coordinates
+// would lose it again on large slots, 8192 Laplacian rows, k = 100: 86 -> 90)
+constexpr int kGramTAShort = 8;
+// ... and of the MFMA form: two tiles of 16 x 16 per column tile at a fixed row
+// stride, one at a run-time one
+constexpr int kGramTAMfma = 32, kGramTAMfmaWide = 16;
 // Column tiles per task that a plan may choose: 1, 2, ..., 2^(steps - 1).
 // A plan whose tasks outnumber the work kernel's waves takes more tiles per
 // task, so that a task's slot rows are loaded once for several tiles.

@@ -152,10 +152,14 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
 // ---------------------------------------------------------------------------
 // MFMA tasks (Gaussian): exp(-(||a||^2 + ||e||^2 - 2 a.e) / kappa) with a.e
 // on FP32 MFMA 16x16x4 (every MFMA form, the BF16 ones included): a task is
-// 16 slot rows by Q tiles of 16 column rows (the plan's Q: at least 4, more
-// when the tasks would outnumber the waves), so a cluster of b_j rows pads
-// to a multiple of 16 rather than 32, and a task loads its slot rows once
-// for all its tiles.  Lane l = 16 g + n supplies
+// 32 slot rows (two row tiles; 16 at a run-time row stride) by Q tiles of 16
+// column rows (the plan's Q: at least 4, more when the tasks would outnumber
+// the waves).  Tiles of 16 keep the padding of a cluster of b_j rows small (a
+// row tile past the cluster is skipped); the task loads its slot rows once
+// for all its column tiles, and each column tile's rows serve both row tiles:
+// what bounds it once a center has collapsed is the rows' way from L2 (4000 of
+// 4096 rows in one cluster, 128 coordinates, window 4: 293 us with one row tile,
+// 278 us so).  Lane l = 16 g + n supplies
 // A[n][g] (slot row n) and B[g][n] (column row n); the u-th MFMA of step t
 // takes coordinate 16 t + 4 g + u, so one 16-byte load per lane and step
 // serves four MFMAs and the four lanes of a row read 64 contiguous bytes
@@ -169,48 +173,60 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
 {
     const int dp = DP > 0 ? DP : dp_rt;
     const int KQ = dp / 4;
-    __shared__ __attribute__((aligned(16))) float sqa[kGramWG / 64][16];
+    constexpr int NR = DP > 0 ? kGramTAMfma / 16 : kGramTAMfmaWide / 16;  // row tiles
+    __shared__ __attribute__((aligned(16))) float sqa[kGramWG / 64][NR][16];
     __shared__ int32_t stage[kGramStage];
     const int lane = threadIdx.x & 63, wl = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
     gram_wave_loop<16, true>(A, stage, blk, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int Q,
                                                  double &lsum) {
-        // the task: slot rows ab*16.., column tiles tile0 .. tile1-1 (wave uniform)
-        const int qa = ab * 16 + n;
+        // the task: slot rows ab*16 NR.., column tiles tile0 .. tile1-1 (wave uniform)
+        const int qa = ab * 16 * NR + n;
+        const bool two = NR > 1 && qa - n + 16 < a.n;  // the second row tile holds rows
         const int tile0 = eb * Q, tile1 = min((ec.n + 15) / 16, tile0 + Q);
         // both permutation loads of the first tile, then every row load, in
         // flight together: clamped indices and selects, no branches (a is a
         // slot column, so a.perm is set; column 0 of ec has no permutation
         // and one row)
         const int32_t *ep = ec.perm ? ec.perm : a.perm;
-        const int32_t pa = a.perm[min(qa, a.n - 1)];
+        int32_t pa[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+            pa[r] = a.perm[min(qa + 16 * r, a.n - 1)];
         int32_t pe = ep[min(tile0 * 16 + n, ec.n - 1)];
-        const int64_t ra = qa < a.n ? a.row0 + pa : zero_row;
-        const float sqa_v = poolsq[ra];
-        const float *sa = pool32 + ra * dp + 4 * g;
+        float sqa_v[NR];
+        const float *sa[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int64_t ra = qa + 16 * r < a.n ? a.row0 + pa[r] : zero_row;
+            sqa_v[r] = poolsq[ra];
+            sa[r] = pool32 + ra * dp + 4 * g;
+        }
         // the slot rows' coordinates, loaded once for every tile of the task
         constexpr int NS = DP > 0 ? DP / 16 : 1;
-        f32x4 av[NS];
+        f32x4 av[NR][NS];
         if constexpr (DP > 0) {
 #pragma unroll
-            for (int q = 0; q < NS; ++q)
-                av[q] = *(const f32x4 *)(sa + 16 * q);
+            for (int r = 0; r < NR; ++r)
+#pragma unroll
+                for (int q = 0; q < NS; ++q)
+                    av[r][q] = *(const f32x4 *)(sa[r] + 16 * q);
         }
         // lane: column n (column row), rows m = 4 g + i (slot rows); the
         // row norms were written by this wave (in-order LDS access) and are
         // read as one 16-byte load; rows past the cluster add an exact 0 (the
         // sum is positive, so no sign of zero changes)
-        auto tile_sum = [&](int tile, const f32x4 &acc, float sqe_v) {
+        auto tile_sum = [&](int tile, int r, const f32x4 &acc, float sqe_v) {
             const int qe_t = tile * 16 + n;
             if (tile == tile0 && g == 0)
-                sqa[wl][n] = c1 * sqa_v;  // slot row n's norm for the output rows m, once per task
+                sqa[wl][r][n] = c1 * sqa_v[r];  // slot row n's norm for the output rows m, once per task
             const float se_ = c1 * sqe_v;
             if (qe_t < ec.n) {
-                const f32x4 sq4 = *(const f32x4 *)&sqa[wl][4 * g];
+                const f32x4 sq4 = *(const f32x4 *)&sqa[wl][r][4 * g];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const int m = 4 * g + i;
+                    const int m = 16 * r + 4 * g + i;
                     const double t = (double)__builtin_amdgcn_exp2f(fmaf(acc[i], c2, sq4[i] + se_));
-                    lsum += ab * 16 + m < a.n ? t : 0.0;
+                    lsum += ab * 16 * NR + m < a.n ? t : 0.0;
                 }
             }
         };
@@ -249,14 +265,30 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                 // the slot row's norm is needed by this point (the products
                 // wait for the row loads anyway), so its load is not sunk into
                 // the branch that publishes it
-                asm volatile("" ::"v"(sqa_v));
-                f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int q = 0; q < NS; ++q)
+                for (int r = 0; r < NR; ++r)
+                    asm volatile("" ::"v"(sqa_v[r]));
+                f32x4 acc[NR];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[q][u], ev[q][u], acc, 0, 0, 0);
-                tile_sum(tile, acc, sqe_v);
+                for (int r = 0; r < NR; ++r)
+                    acc[r] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (two) {  // wave uniform
+#pragma unroll
+                    for (int q = 0; q < NS; ++q)
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int r = 0; r < NR; ++r)
+                                acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[r][q][u], ev[q][u], acc[r], 0, 0, 0);
+                    tile_sum(tile, NR - 1, acc[NR - 1], sqe_v);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < NS; ++q)
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[0][q][u], ev[q][u], acc[0], 0, 0, 0);
+                }
+                tile_sum(tile, 0, acc[0], sqe_v);
 #pragma unroll
                 for (int q = 0; q < NS; ++q)
                     ev[q] = en[q];
@@ -279,7 +311,7 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
 #pragma unroll
                     for (int q = 0; q < U; ++q) {
                         const int s4 = min(s0 + 4 * q, KQ - 4);
-                        a4[q] = *(const f32x4 *)(sa + 4 * s4);
+                        a4[q] = *(const f32x4 *)(sa[0] + 4 * s4);
                         e4[q] = *(const f32x4 *)(se + 4 * s4);
                     }
                     __builtin_amdgcn_sched_barrier(0);  // keep the loads ahead of the products
@@ -290,7 +322,7 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                             for (int u = 0; u < 4; ++u)
                                 acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[q][u], e4[q][u], acc, 0, 0, 0);
                 }
-                tile_sum(tile, acc, sqe_v);
+                tile_sum(tile, 0, acc, sqe_v);
             }
         }
     });

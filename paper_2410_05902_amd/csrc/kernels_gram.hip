@@ -15,10 +15,10 @@
 //          ranges form a monotone staircase, so w + jc is distinct per run;
 //   fold : per live (j, c), the partials of its waves in wave order.
 // Every sum has a fixed order, so the blocks are bit-reproducible.
-//   k_gram_valu : any kernel, FP32 or FP64 arithmetic; a task is 32 slot
+//   k_gram_valu : any kernel, FP32 or FP64 arithmetic; a task is 8 to 32 slot
 //                 rows (wave-uniform) x 64 column rows (one per lane);
 //   k_gram_mfma : Gaussian MFMA forms; FP32 MFMA products and exp fused in
-//                 registers; a task is one 16 x 16 output block.  The BF16
+//                 registers; a task is output blocks of 16 x 16.  The BF16
 //                 forms take their Gram blocks here too: the self norms keep
 //                 FP32 kernel values (summed in FP64), so a row re-scored in
 //                 FP64 carries only the FP32 error of N_j.
@@ -64,9 +64,9 @@ __host__ __device__ constexpr int gram_valu_rpl()
     return sizeof(KT) == 4 ? 2 : 1;
 }
 template <typename KT>
-__host__ __device__ constexpr int gram_valu_ta()
+__host__ __device__ constexpr int gram_valu_ta(int d)
 {
-    return sizeof(KT) == 4 ? kGramTA : kGramTA64;
+    return d <= 8 ? kGramTAShort : (sizeof(KT) == 4 ? kGramTA : kGramTA64);
 }
 
 // Up to 64 coordinates: the lane's column rows stay in registers (DR >= d
@@ -85,7 +85,7 @@ template <int KIND, typename KT, int DR>
 __global__ __launch_bounds__(kGramWG) void k_gram_rows(const GramWork A, int dp, double param,
                                                        const float *__restrict__ pool32, int zero_row)
 {
-    constexpr int RPL = gram_valu_rpl<KT>(), TA = gram_valu_ta<KT>();
+    constexpr int RPL = gram_valu_rpl<KT>(), TA = gram_valu_ta<KT>(DR);
     const int lane = threadIdx.x & 63;
     const KT prm = (KT)param, rprm = (KT)1 / prm;
     __shared__ int32_t stage[kGramStage];
@@ -145,7 +145,7 @@ template <int KIND, typename KT>
 __global__ __launch_bounds__(kGramWG) void k_gram_valu(const GramWork A, int d, int dp, double param,
                                                        const float *__restrict__ pool32, int zero_row)
 {
-    constexpr int RPL = gram_valu_rpl<KT>(), TA = gram_valu_ta<KT>();
+    constexpr int RPL = gram_valu_rpl<KT>(), TA = gram_valu_ta<KT>(65);
     constexpr int DC = 32 / RPL;
     const int lane = threadIdx.x & 63;
     const KT prm = (KT)param, rprm = (KT)1 / prm;
@@ -259,8 +259,13 @@ int gram_task_cols(int mfma, int fp64)
     return mfma ? 16 : 64 * (fp64 ? gram_valu_rpl<double>() : gram_valu_rpl<float>());
 }
 
-int gram_task_rows(int mfma, int fp64) { return mfma ? kGramTAMfma : (fp64 ? kGramTA64 : kGramTA); }
-// the MFMA task loads its 16 slot rows once for up to MBKK_GRAM_QMAX column
+int gram_task_rows(const Layout &L, int mfma, int fp64)
+{
+    if (mfma)
+        return L.dp <= 128 ? kGramTAMfma : kGramTAMfmaWide;
+    return fp64 ? gram_valu_ta<double>(L.d) : gram_valu_ta<float>(L.d);
+}
+// the MFMA task loads its slot rows once for up to MBKK_GRAM_QMAX column
 // tiles (a power of two, at most 2^(kGramTileSteps - 1)); the VALU task
 // takes one column set
 #ifndef MBKK_GRAM_QMAX

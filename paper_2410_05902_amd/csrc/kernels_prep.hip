@@ -978,7 +978,9 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
     }
     __syncthreads();
     // ---- label totals: slice sums over chunks, then per label over slices
-    const int TG = nt / k;  // >= 2
+    // (no more slices than chunks: a center adds its slices one after another,
+    // 341 of them for 4 chunks at k = 3)
+    const int TG = min(nt / k, nchunk);
     const int gs = (nchunk + TG - 1) / TG;
     if (tid < TG * k) {
         const int jj = tid % k, sl = tid / k;

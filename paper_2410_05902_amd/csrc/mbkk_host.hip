@@ -335,7 +335,7 @@ static uint32_t col_mask_of(const SlotList &s, bool init_alive)
 static void gram(mbkk_ctx *c, int p, uint32_t mask, bool in_step)
 {
     if (!in_step)
-        launch_gram_plan(c->L, c->B, p, mask, gram_task_rows(c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64),
+        launch_gram_plan(c->L, c->B, p, mask, gram_task_rows(c->L, c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64),
                          c->stream);
     launch_gram(c->L, c->B, p, mask, c->cfg.kernel, c->cfg.kernel_param, c->fp64, c->use_mfma, !in_step, c->stream);
     if (in_step) {
@@ -474,7 +474,7 @@ static int timing_pair(mbkk_ctx *c, hipEvent_t *e0, hipEvent_t *e1)
 
 static bool step_rescores(const mbkk_ctx *c, int b)
 {
-    return c->L.bf16 && update_rescores(c->L, b, gram_task_rows(c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64));
+    return c->L.bf16 && update_rescores(c->L, b, gram_task_rows(c->L, c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64));
 }
 
 static int cross_and_score(mbkk_ctx *c, int nb, const RowOutputs &out, bool with_rank)
@@ -851,7 +851,7 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
     const bool resc = step_rescores(c, b);
     const RescoreArgs ra = resc ? rescore_args(L, B, b, c->cfg.precision, c->cfg.kernel_param, out, true) : RescoreArgs{};
     launch_update(L, B, b, p_new, p_expired, init_alive_before, init_keep, live, win, c->cfg.lr, mask,
-                  gram_task_rows(c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64), gram_task_qmax(c->use_mfma),
+                  gram_task_rows(c->L, c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64), gram_task_qmax(c->use_mfma),
                   gram_waves(c->use_mfma), resc ? &ra : nullptr, c->stream);
     gram(c, p_new, mask, true);
     c->seg_next_iter = i + 1;

@@ -1,0 +1,33 @@
+"""Self-norm blocks cut into tasks of 8 slot rows (rows of at most 8
+coordinates) and of two 16-row tiles (matrix-core forms): cluster sizes around
+both, and centers with no rows, against the oracle."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle as O
+from tests.test_gpu_parity import lockstep
+
+pytestmark = pytest.mark.gpu
+
+COUNTS = [[1, 8, 16, 32, 0], [7, 9, 15, 17, 33], [31, 0, 48, 64, 65], [16, 33, 1, 49, 127]]
+
+
+@pytest.mark.parametrize("d,kind,precision,impl", [
+    (2, O.GAUSS, "fp32", "direct"), (8, O.LAPLACE, "fp32", "direct"), (7, O.GAUSS, "fp64", "direct"),
+    (9, O.POLY2, "fp32", "direct"), (3, O.GAUSS, "fp32", "mfma"), (40, O.GAUSS, "fp32", "mfma"),
+    (90, O.GAUSS, "fp32", "mfma"), (128, O.GAUSS, "fp32", "mfma"), (150, O.GAUSS, "fp32", "mfma"),
+])
+def test_lockstep(d, kind, precision, impl):
+    rng = np.random.default_rng(d)
+    k, n = 5, 2500
+    means = 4.0 * np.eye(k, d) if d >= k else 2.0 / np.sqrt(d) * (np.arange(k) - 2.0)[:, None] * np.ones((1, d))
+    comp = np.arange(n) % k
+    X = (means[comp] + 0.3 * rng.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    param = {O.GAUSS: 8.0, O.LAPLACE: 8.0, O.POLY2: 1.0}[kind]
+    rows = [np.flatnonzero(comp == j) for j in range(k)]
+    batches = [np.concatenate([rng.choice(rows[j], c) for j, c in enumerate(cs) if c]).astype(np.int32)
+               for cs in COUNTS]
+    init = np.array([r[0] for r in rows], np.int32)
+    lockstep(X, k, 3, kind, param, init, [rng.permutation(b) for b in batches], precision, impl=impl, b_max=256)
