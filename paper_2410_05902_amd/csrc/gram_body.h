@@ -126,26 +126,26 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
         return;  // wave uniform
     const int t0 = (int)t0l, t1 = min(T, t0 + chunk);
     int jc = __builtin_amdgcn_readfirstlane(wave_segment_of(goff, nJC, t0));
-    int t = t0;
-    while (t < t1) {  // wave uniform
-        const int g0 = __builtin_amdgcn_readfirstlane(goff[jc]), g1 = __builtin_amdgcn_readfirstlane(goff[jc + 1]);
-        const int e = min(t1, g1);
-        if (t < e) {
-            const int j = jc / A.C, c = jc - j * A.C;
-            const GramCol a = gram_col_uniform(A.k, A.bmax, j, 1 + A.rr, ring_off, A.ring_perm);
-            const GramCol ec = gram_col_uniform(A.k, A.bmax, j, c, ring_off, A.ring_perm);
-            const int nE = ((ec.n + TE - 1) / TE + Q - 1) / Q;
-            double lsum = 0.0;
-            for (; t < e; ++t) {
-                const int u = t - g0;
-                const int ab = u / nE, eb = u - ab * nE;
-                task(a, ec, ab, eb, Q, lsum);
-            }
-            lsum = wave_sum_f64(lsum);
-            if (lane == 0)
-                A.gpart[w + jc] = lsum;
+    int t = t0, g0 = __builtin_amdgcn_readfirstlane(goff[jc]);
+    for (;;) {  // wave uniform
+        const int e = min(t1, __builtin_amdgcn_readfirstlane(goff[jc + 1]));
+        const int j = jc / A.C, c = jc - j * A.C;
+        const GramCol a = gram_col_uniform(A.k, A.bmax, j, 1 + A.rr, ring_off, A.ring_perm);
+        const GramCol ec = gram_col_uniform(A.k, A.bmax, j, c, ring_off, A.ring_perm);
+        const int nE = ((ec.n + TE - 1) / TE + Q - 1) / Q;
+        double lsum = 0.0;
+        for (; t < e; ++t) {
+            const int u = t - g0;
+            const int ab = u / nE, eb = u - ab * nE;
+            task(a, ec, ab, eb, Q, lsum);
         }
-        ++jc;
+        lsum = wave_sum_f64(lsum);
+        if (lane == 0)
+            A.gpart[w + jc] = lsum;
+        if (t >= t1)
+            return;
+        jc = __builtin_amdgcn_readfirstlane(wave_next_segment(goff, nJC, jc, t));
+        g0 = t;
     }
 }
 

@@ -180,9 +180,7 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
                         P[(int64_t)id * ldp + row[q]] = (T)acc[q];
                     acc[q] = 0;
                 }
-                do {
-                    ++j;
-                } while (seg_off[j + 1] <= s);
+                j = wave_next_segment(seg_off, k, j, s);
                 cur_end = min(s1, seg_off[j + 1]);
                 id = j;
             }

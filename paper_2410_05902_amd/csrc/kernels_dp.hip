@@ -479,9 +479,7 @@ __global__ __launch_bounds__(kDpTableWG) void k_dp_table(int64_t n, int d, int64
                 const int s = c0 + e;
                 if (s >= cur_end) {
                     flush();
-                    do {
-                        ++j;
-                    } while (seg[j + 1] <= s);
+                    j = wave_next_segment(seg, k, j, s);
                     begin();
                 }
                 const float *__restrict__ y = pool32 + (int64_t)__builtin_amdgcn_readlane(lrow, e) * dp;

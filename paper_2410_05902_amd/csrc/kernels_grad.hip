@@ -383,7 +383,8 @@ __global__ __launch_bounds__(256) void k_sigma_gram(const SigmaGramArgs A)
                 A.part2[w + j] = ld;
             }
         }
-        ++j;
+        if (t < t1)
+            j = wave_next_segment(A.toff, A.k, j, t);
     }
 }
 

@@ -31,3 +31,20 @@ def test_lockstep(d, kind, precision, impl):
                for cs in COUNTS]
     init = np.array([r[0] for r in rows], np.int32)
     lockstep(X, k, 3, kind, param, init, [rng.permutation(b) for b in batches], precision, impl=impl, b_max=256)
+
+
+@pytest.mark.parametrize("d,kind,precision,impl", [
+    (5, O.LAPLACE, "fp32", "direct"), (20, O.GAUSS, "fp64", "direct"), (40, O.GAUSS, "fp32", "mfma"),
+])
+@pytest.mark.parametrize("used", [[0, 499], [3, 67, 68, 132, 498], [250]])
+def test_empty_centers(d, kind, precision, impl, used):
+    # runs of empty centers shorter and longer than a wave between those with rows
+    rng = np.random.default_rng(d + len(used))
+    k, n = 500, 2000
+    means = rng.standard_normal((k, d)) * 3.0
+    comp = np.arange(n) % k
+    X = (means[comp] + 0.1 * rng.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    rows = np.flatnonzero(np.isin(comp, used))
+    init = np.arange(k, dtype=np.int32)
+    batches = [rng.choice(rows, 150).astype(np.int32) for _ in range(4)]
+    lockstep(X, k, 4, kind, 4.0 * d, init, batches, precision, impl=impl, b_max=256)
