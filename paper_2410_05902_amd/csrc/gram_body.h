@@ -66,7 +66,7 @@ __device__ __forceinline__ GramCol gram_col_uniform(int k, int bmax, int j, int 
 // (pblk % 8); the workgroups that have tasks are cut into 8 contiguous
 // shares, share x taken by the workgroups of XCD x, so that the tasks of a
 // center, which are contiguous, read their rows through one XCD's L2.
-template <int TE, bool TQ, class Task>
+template <int TA, int TE, bool TQ, class Task>
 __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage, int pblk, Task &&task)
 {
     const int lane = threadIdx.x & 63;
@@ -133,11 +133,27 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
         const GramCol a = gram_col_uniform(A.k, A.bmax, j, 1 + A.rr, ring_off, A.ring_perm);
         const GramCol ec = gram_col_uniform(A.k, A.bmax, j, c, ring_off, A.ring_perm);
         const int nE = ((ec.n + TE - 1) / TE + Q - 1) / Q;
+        // the slot's own block, by the tasks on and above the diagonal: column
+        // eb of tasks starts at task r eb (eb + 1) / 2 and holds the row blocks
+        // up to r (eb + 1), its last r on the diagonal
+        const bool half = gram_half(c == 1 + A.rr, __builtin_ctz(TA), __builtin_ctz((unsigned)(TE * Q)));
+        const int r = max(1, TE * Q / TA);
         double lsum = 0.0;
         for (; t < e; ++t) {
             const int u = t - g0;
-            const int ab = u / nE, eb = u - ab * nE;
-            task(a, ec, ab, eb, Q, lsum);
+            int ab, eb;
+            if (half) {
+                eb = (int)((sqrtf(1.0f + 8.0f * (float)(u / r)) - 1.0f) * 0.5f);
+                eb -= r * eb * (eb + 1) / 2 > u;
+                eb += r * (eb + 1) * (eb + 2) / 2 <= u;
+                ab = u - r * eb * (eb + 1) / 2;
+            } else {
+                ab = u / nE;
+                eb = u - ab * nE;
+            }
+            double ls = 0.0;
+            task(a, ec, ab, eb, Q, ls);
+            lsum += half && ab < r * eb ? 2.0 * ls : ls;
         }
         lsum = wave_sum_f64(lsum);
         if (lane == 0)
@@ -159,7 +175,8 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
 // for all its column tiles, and each column tile's rows serve both row tiles:
 // what bounds it once a center has collapsed is the rows' way from L2 (4000 of
 // 4096 rows in one cluster, 128 coordinates, window 4: 293 us with one row tile,
-// 278 us so).  Lane l = 16 g + n supplies
+// 278 us so, 220 us with
+// the slot's own block halved).  Lane l = 16 g + n supplies
 // A[n][g] (slot row n) and B[g][n] (column row n); the u-th MFMA of step t
 // takes coordinate 16 t + 4 g + u, so one 16-byte load per lane and step
 // serves four MFMAs and the four lanes of a row read 64 contiguous bytes
@@ -177,7 +194,7 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
     __shared__ __attribute__((aligned(16))) float sqa[kGramWG / 64][NR][16];
     __shared__ int32_t stage[kGramStage];
     const int lane = threadIdx.x & 63, wl = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
-    gram_wave_loop<16, true>(A, stage, blk, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int Q,
+    gram_wave_loop<16 * NR, 16, true>(A, stage, blk, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int Q,
                                                  double &lsum) {
         // the task: slot rows ab*16 NR.., column tiles tile0 .. tile1-1 (wave uniform)
         const int qa = ab * 16 * NR + n;

@@ -76,9 +76,9 @@ __host__ __device__ constexpr int gram_valu_ta(int d)
 // coordinate and pair (FP64: also a conversion per coordinate) and the
 // exponential, about 95 instructions a pair at 32 coordinates.  The general
 // kernel below keeps the sums of 32 slot rows in registers instead, which
-// leaves room for 16 coordinates at a time: 890 us against 765 us here for a
-// cluster of 8191 of 8192 rows (32 coordinates, window 4, 2.7e8 pairs), and
-// 28 us against 16 us in FP64 (64 coordinates, k = 50, b = 1024).  Sums over
+// leaves room for 16 coordinates at a time: 28 us against 16 us in
+// FP64 (64 coordinates, k = 50, b = 1024); in FP32 a cluster of 8191 of 8192 rows
+// (32 coordinates) takes 1.7 us per 1e6 pairs here.  Sums over
 // the coordinates run in the same order in both, so the kernel values are the
 // same bits.
 template <int KIND, typename KT, int DR>
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kGramWG) void k_gram_rows(const GramWork A, int dp,
     const int lane = threadIdx.x & 63;
     const KT prm = (KT)param, rprm = (KT)1 / prm;
     __shared__ int32_t stage[kGramStage];
-    gram_wave_loop<64 * RPL, false>(A, stage, blockIdx.x, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int,
+    gram_wave_loop<TA, 64 * RPL, false>(A, stage, blockIdx.x, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int,
                                                               double &lsum) {
         bool eok[RPL];
         KT ev[RPL][DR];
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kGramWG) void k_gram_valu(const GramWork A, int d, 
     const KT prm = (KT)param, rprm = (KT)1 / prm;
     __shared__ int32_t stage[kGramStage];
     // (one column set per task: the VALU plan takes Q = 1)
-    gram_wave_loop<64 * RPL, false>(A, stage, blockIdx.x, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int,
+    gram_wave_loop<TA, 64 * RPL, false>(A, stage, blockIdx.x, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int,
                                                               double &lsum) {
         bool eok[RPL];
         int re[RPL];

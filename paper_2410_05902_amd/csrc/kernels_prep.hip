@@ -1023,10 +1023,12 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
     // ---- learning rate and the coefficient update of center j
     int tasks[kGramTileSteps] = {};  // Gram tasks of 1, 2, 4, ... column tiles
     int slen = 0;
-    int nA = 0, ntl[kGroupSmallC];  // slot-row tiles, and column tiles of the counted columns (else 0)
+    // the slot's own row count where its column is counted, and the rows of the
+    // other counted columns (else 0)
+    int nown = 0, nel[kGroupSmallC];
 #pragma unroll
     for (int c = 0; c < kGroupSmallC; ++c)
-        ntl[c] = 0;
+        nel[c] = 0;
     if (own) {
         double a;
         if (lr == MBKK_LR_FULL)
@@ -1092,18 +1094,22 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
         // Gram tasks of the new slot against the live columns that keep a
         // weight (for each number of column tiles per task), and the padded
         // segment of center j in the next support
-        nA = (bj + gram_ta - 1) >> lta;
 #pragma unroll
         for (int c = 0; c < kGroupSmallC; ++c) {
             if (c < C && ((gram_mask >> c) & 1u) && cf[c] != 0.0) {
                 const int nec = c == 0 ? 1 : (c - 1 == p_new ? bj : ne[c]);
-                ntl[c] = (nec + gram_te - 1) >> lte;
+                const bool ownc = c - 1 == p_new;
+                nown = ownc ? bj : nown;
+                nel[c] = ownc ? 0 : nec;
 #pragma unroll
                 for (int qi = 0; qi < kGramTileSteps; ++qi)
-                    tasks[qi] += nA * ((ntl[c] + (1 << qi) - 1) >> qi);
+                    tasks[qi] += gram_block_tasks(bj, nel[c], lta, lte + qi, false);
                 slen += nec;
             }
         }
+#pragma unroll
+        for (int qi = 0; qi < kGramTileSteps; ++qi)
+            tasks[qi] += gram_block_tasks(bj, nown, lta, lte + qi, true);
         slen = seg_padded_len(slen, pad, packed);
     }
     int sv[1 + kGramTileSteps], srun_[1 + kGramTileSteps], stot[1 + kGramTileSteps];
@@ -1126,11 +1132,12 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
         seg_next[k] = seg_padded_end(stot[0], pad, packed);
     if (own) {
         int trun = srun_[1 + qi];
+        const int town = gram_block_tasks(bj, nown, lta, lte + qi, true);
 #pragma unroll
         for (int c = 0; c < kGroupSmallC; ++c) {
             if (c < C) {
                 goff[(int64_t)j * C + c] = trun;
-                trun += nA * ((ntl[c] + Q - 1) >> qi);
+                trun += gram_block_tasks(bj, nel[c], lta, lte + qi, false) + (c - 1 == p_new ? town : 0);
             }
         }
     }
