@@ -48,3 +48,23 @@ def test_empty_centers(d, kind, precision, impl, used):
     init = np.arange(k, dtype=np.int32)
     batches = [rng.choice(rows, 150).astype(np.int32) for _ in range(4)]
     lockstep(X, k, 4, kind, 4.0 * d, init, batches, precision, impl=impl, b_max=256)
+
+
+@pytest.mark.parametrize("d,kind,precision,impl", [
+    (5, O.LAPLACE, "fp32", "direct"), (20, O.GAUSS, "fp64", "direct"), (40, O.GAUSS, "fp32", "mfma"),
+    (150, O.GAUSS, "fp32", "mfma"),
+])
+@pytest.mark.parametrize("sizes", [[1023, 1024, 1024, 1000], [1023, 1025, 1100], [2047, 300], [1, 2500, 5]])
+def test_large_center(d, kind, precision, impl, sizes):
+    # supports of one center below, at and past 2048 entries, laid out slot by slot
+    # (with its initial point while that has a weight), beside a small one
+    rng = np.random.default_rng(d + sum(sizes))
+    k, n = 3, 3000
+    means = 3.0 * np.eye(k, d)
+    comp = np.where(np.arange(n) < 60, np.arange(n) % k, 1)
+    X = (means[comp] + 0.4 * rng.standard_normal((n, d)) / np.sqrt(d)).astype(np.float32)
+    big, small = np.flatnonzero(comp == 1), np.flatnonzero(comp == 2)
+    batches = [rng.permutation(np.concatenate([rng.choice(big, s), rng.choice(small, 3)])).astype(np.int32)
+               for s in sizes]
+    batches.append(batches[0][:100].copy())
+    lockstep(X, k, 3, kind, 8.0, np.arange(k, dtype=np.int32), batches, precision, impl=impl, b_max=2560)
