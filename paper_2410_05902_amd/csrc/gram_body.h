@@ -189,9 +189,11 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                                                float c2, float c1, int blk)
 {
     const int dp = DP > 0 ? DP : dp_rt;
-    const int KQ = dp / 4;
     constexpr int NR = DP > 0 ? kGramTAMfma / 16 : kGramTAMfmaWide / 16;  // row tiles
     __shared__ __attribute__((aligned(16))) float sqa[kGramWG / 64][NR][16];
+    // a wave's rows on their way to the products (run-time row stride): 16 slot
+    // rows, then 16 column rows, of 32 coordinates and 4 of padding
+    __shared__ __attribute__((aligned(16))) float xch[DP > 0 ? 1 : kGramWG / 64][DP > 0 ? 1 : 32][36];
     __shared__ int32_t stage[kGramStage];
     const int lane = threadIdx.x & 63, wl = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
     gram_wave_loop<16 * NR, 16, true>(A, stage, blk, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int Q,
@@ -211,10 +213,12 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
             pa[r] = a.perm[min(qa + 16 * r, a.n - 1)];
         int32_t pe = ep[min(tile0 * 16 + n, ec.n - 1)];
         float sqa_v[NR];
+        int64_t ra_w = zero_row;  // (one row tile: its row)
         const float *sa[NR];
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             const int64_t ra = qa + 16 * r < a.n ? a.row0 + pa[r] : zero_row;
+            ra_w = ra;
             sqa_v[r] = poolsq[ra];
             sa[r] = pool32 + ra * dp + 4 * g;
         }
@@ -317,27 +321,59 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                     pe = ep[min(tile * 16 + n, ec.n - 1)];
                 const int64_t re = col_row(tile, pe);
                 const float sqe_v = poolsq[re];
-                const float *se = pool32 + re * dp + 4 * g;
                 f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
-                // row stride at run time: 8 steps of 4 coordinates per round
-                // of loads, all in flight before their products (clamped
-                // indices; the steps past the row skip their products)
-                constexpr int U = 8;
-                for (int s0 = 0; s0 < KQ; s0 += 4 * U) {
-                    f32x4 a4[U], e4[U];
+                // row stride at run time: 32 coordinates of the 16 + 16 rows at
+                // a time, loaded as whole cache lines (8 lanes per row, NC
+                // chunks in flight) and handed to the lanes of the products
+                // through the wave's LDS.  Loaded by those lanes themselves (16
+                // rows x 64 bytes per load) the half lines bound the kernel, at
+                // 15 bytes per clock and unit: 784 coordinates, k = 10, b = 1024,
+                // window 8: 54 us, 29 us so.
+                constexpr int NC = 4;
+                const int lr = lane >> 3, lc = 4 * (lane & 7), nch = dp / 32;
+                const int ra0 = (int)ra_w, re0 = (int)re;
+                const float *src[4];
 #pragma unroll
-                    for (int q = 0; q < U; ++q) {
-                        const int s4 = min(s0 + 4 * q, KQ - 4);
-                        a4[q] = *(const f32x4 *)(sa[0] + 4 * s4);
-                        e4[q] = *(const f32x4 *)(se + 4 * s4);
+                for (int h = 0; h < 2; ++h) {
+                    src[h] = pool32 + (int64_t)__shfl(ra0, lr + 8 * h) * dp + lc;
+                    src[2 + h] = pool32 + (int64_t)__shfl(re0, lr + 8 * h) * dp + lc;
+                }
+                auto take = [&](const f32x4 (&v)[4]) {
+                    // (a wave's LDS accesses take place in order: the fences
+                    // keep the compiler's order, no barrier is needed)
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int h = 0; h < 4; ++h)
+                        *(f32x4 *)&xch[wl][lr + 8 * h][lc] = v[h];
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const f32x4 a4 = *(const f32x4 *)&xch[wl][n][16 * t + 4 * g];
+                        const f32x4 e4 = *(const f32x4 *)&xch[wl][16 + n][16 * t + 4 * g];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[u], e4[u], acc, 0, 0, 0);
                     }
+                };
+                int c0 = 0;
+                for (; c0 + NC <= nch; c0 += NC) {
+                    f32x4 v[NC][4];
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int h = 0; h < 4; ++h)
+                            v[c][h] = *(const f32x4 *)(src[h] + 32 * (c0 + c));
                     __builtin_amdgcn_sched_barrier(0);  // keep the loads ahead of the products
 #pragma unroll
-                    for (int q = 0; q < U; ++q)
-                        if (s0 + 4 * q < KQ)  // wave uniform
+                    for (int c = 0; c < NC; ++c)
+                        take(v[c]);
+                }
+                for (; c0 < nch; ++c0) {
+                    f32x4 v[4];
 #pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[q][u], e4[q][u], acc, 0, 0, 0);
+                    for (int h = 0; h < 4; ++h)
+                        v[h] = *(const f32x4 *)(src[h] + 32 * c0);
+                    take(v);
                 }
                 tile_sum(tile, 0, acc, sqe_v);
             }
