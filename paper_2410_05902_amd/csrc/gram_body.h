@@ -176,11 +176,10 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
 // what bounds it once a center has collapsed is the rows' way from L2 (4000 of
 // 4096 rows in one cluster, 128 coordinates, window 4: 293 us with one row tile,
 // 278 us so, 220 us with
-// the slot's own block halved).  Lane l = 16 g + n supplies
+// the slot's own block halved, 198 us with the rows loaded as whole lines).  Lane l = 16 g + n supplies
 // A[n][g] (slot row n) and B[g][n] (column row n); the u-th MFMA of step t
 // takes coordinate 16 t + 4 g + u, so one 16-byte load per lane and step
-// serves four MFMAs and the four lanes of a row read 64 contiguous bytes
-// (16 cache lines per wave load, not 64).  The lane holds D[4 g + i][n], i < 4.
+// serves four MFMAs.  The lane holds D[4 g + i][n], i < 4.
 // DP = 0 takes the row stride at run time.  blk: the physical workgroup index.
 // ---------------------------------------------------------------------------
 template <int DP>
@@ -191,9 +190,10 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
     const int dp = DP > 0 ? DP : dp_rt;
     constexpr int NR = DP > 0 ? kGramTAMfma / 16 : kGramTAMfmaWide / 16;  // row tiles
     __shared__ __attribute__((aligned(16))) float sqa[kGramWG / 64][NR][16];
-    // a wave's rows on their way to the products (run-time row stride): 16 slot
-    // rows, then 16 column rows, of 32 coordinates and 4 of padding
-    __shared__ __attribute__((aligned(16))) float xch[DP > 0 ? 1 : kGramWG / 64][DP > 0 ? 1 : 32][36];
+    // a wave's rows on their way to the products: a tile of 16 rows (run-time
+    // row stride: 16 slot rows, then 16 column rows, of 32 coordinates), padded
+    // by 4 coordinates
+    __shared__ __attribute__((aligned(16))) float xch[kGramWG / 64][DP > 0 ? 16 : 32][(DP > 0 ? DP : 32) + 4];
     __shared__ int32_t stage[kGramStage];
     const int lane = threadIdx.x & 63, wl = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
     gram_wave_loop<16 * NR, 16, true>(A, stage, blk, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int Q,
@@ -213,24 +213,51 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
             pa[r] = a.perm[min(qa + 16 * r, a.n - 1)];
         int32_t pe = ep[min(tile0 * 16 + n, ec.n - 1)];
         float sqa_v[NR];
-        int64_t ra_w = zero_row;  // (one row tile: its row)
-        const float *sa[NR];
+        int64_t ra_w[NR];
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             const int64_t ra = qa + 16 * r < a.n ? a.row0 + pa[r] : zero_row;
-            ra_w = ra;
+            ra_w[r] = ra;
             sqa_v[r] = poolsq[ra];
-            sa[r] = pool32 + ra * dp + 4 * g;
         }
-        // the slot rows' coordinates, loaded once for every tile of the task
+        // A tile's rows are loaded as whole cache lines, 8 lanes of 16 bytes per
+        // line and 8 rows per load, and handed to the lanes of the products
+        // through the wave's LDS (lane (n, g) takes 4 coordinates of row n from
+        // 16 q + 4 g).  Loaded by those lanes themselves, 16 rows x 64 bytes, the
+        // half lines bound the kernel, at 15 bytes per clock and unit (128 coordinates:
+        // 12.4 -> 11.9 us a balanced step, 220 -> 198 with one center holding 4000 of
+        // 4096 rows; 64: 111 -> 106; 784 below)
+        const int lr = lane >> 3, lc = 4 * (lane & 7);
         constexpr int NS = DP > 0 ? DP / 16 : 1;
+        auto load_rows = [&](int64_t row, f32x4 (&v)[NS]) {  // row: of lane n's row n
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float *src = pool32 + (int64_t)__shfl((int)row, lr + 8 * h) * dp + lc;
+#pragma unroll
+                for (int c = 0; c < NS / 2; ++c)
+                    v[2 * c + h] = *(const f32x4 *)(src + 32 * c);
+            }
+        };
+        auto pass_rows = [&](const f32x4 (&v)[NS], f32x4 (&o)[NS]) {
+            // (a wave's LDS accesses take place in order: the fences keep the
+            // compiler's order, no barrier is needed)
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int c = 0; c < NS / 2; ++c)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    *(f32x4 *)&xch[wl][lr + 8 * h][32 * c + lc] = v[2 * c + h];
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < NS; ++q)
+                o[q] = *(const f32x4 *)&xch[wl][n][16 * q + 4 * g];
+        };
+        // the slot rows' coordinates, loaded once for every tile of the task
         f32x4 av[NR][NS];
         if constexpr (DP > 0) {
 #pragma unroll
             for (int r = 0; r < NR; ++r)
-#pragma unroll
-                for (int q = 0; q < NS; ++q)
-                    av[r][q] = *(const f32x4 *)(sa[r] + 16 * q);
+                load_rows(ra_w[r], av[r]);
         }
         // lane: column n (column row), rows m = 4 g + i (slot rows); the
         // row norms were written by this wave (in-order LDS access) and are
@@ -267,10 +294,11 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                 pes[q] = ep[min(min(tile0 + q, tile1 - 1) * 16 + n, ec.n - 1)];
             int64_t re = col_row(tile0, pes[0]);
             float sqe_v = poolsq[re];
-            f32x4 ev[NS];
-#pragma unroll
-            for (int q = 0; q < NS; ++q)
-                ev[q] = *(const f32x4 *)(pool32 + re * dp + 4 * g + 16 * q);
+            f32x4 en[NS];
+            load_rows(re, en);
+            pass_rows(av[0], av[0]);
+            if (two)  // wave uniform
+                pass_rows(av[NR - 1], av[NR - 1]);
 #pragma unroll
             for (int t = 0; t < QX; ++t) {
                 const int tile = tile0 + t;
@@ -279,10 +307,9 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                 const int tn = min(tile + 1, tile1 - 1);
                 const int64_t rn = col_row(tn, pes[t + 1 < QX ? t + 1 : t]);
                 const float sqn = poolsq[rn];
-                f32x4 en[NS];
-#pragma unroll
-                for (int q = 0; q < NS; ++q)
-                    en[q] = *(const f32x4 *)(pool32 + rn * dp + 4 * g + 16 * q);
+                f32x4 ev[NS];
+                pass_rows(en, ev);
+                load_rows(rn, en);
                 // the slot row's norm is needed by this point (the products
                 // wait for the row loads anyway), so its load is not sunk into
                 // the branch that publishes it
@@ -310,9 +337,6 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                             acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[0][q][u], ev[q][u], acc[0], 0, 0, 0);
                 }
                 tile_sum(tile, 0, acc[0], sqe_v);
-#pragma unroll
-                for (int q = 0; q < NS; ++q)
-                    ev[q] = en[q];
                 sqe_v = sqn;
             }
         } else {
@@ -323,15 +347,11 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                 const float sqe_v = poolsq[re];
                 f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
                 // row stride at run time: 32 coordinates of the 16 + 16 rows at
-                // a time, loaded as whole cache lines (8 lanes per row, NC
-                // chunks in flight) and handed to the lanes of the products
-                // through the wave's LDS.  Loaded by those lanes themselves (16
-                // rows x 64 bytes per load) the half lines bound the kernel, at
-                // 15 bytes per clock and unit: 784 coordinates, k = 10, b = 1024,
-                // window 8: 54 us, 29 us so.
+                // a time, NC such chunks in flight (784 coordinates, k = 10,
+                // b = 1024, window 8: 54 us by half lines, 29 us so)
                 constexpr int NC = 4;
-                const int lr = lane >> 3, lc = 4 * (lane & 7), nch = dp / 32;
-                const int ra0 = (int)ra_w, re0 = (int)re;
+                const int nch = dp / 32;
+                const int ra0 = (int)ra_w[0], re0 = (int)re;
                 const float *src[4];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
