@@ -223,16 +223,41 @@ __device__ __forceinline__ int wave_next_segment(const int32_t *__restrict__ off
     }
 }
 
-// s / c for s >= 0, correctly rounded, from r = 1 / c correctly rounded: the
-// rounded product and one correction by its exact residual (Markstein), three
-// operations instead of the ten or more of a division.  A product that
-// overflows, or s = inf, gives inf as the division does; NaN stays NaN.
+// s / c for s >= 0, from r = 1 / c correctly rounded: the rounded product and
+// one correction by its exact residual (Markstein), three operations instead of
+// the ten or more of a division.  A product that overflows, or s = inf, gives
+// inf as the division does; NaN stays NaN.  This needs div_by_holds(c): the
+// reciprocal is then normal and the residual exact for every q with
+// exp(-q) != 1, so that exp gets what the division would give.
 template <typename T>
 __device__ __forceinline__ T div_by(T s, T c, T r)
 {
     const T q = s * r;
     const T e = fma(-q, c, s);
     return q < (T)INFINITY ? fma(e, r, q) : q;
+}
+
+// Quotients q >= 2^(-p-1) matter, p = 24 (53): the product q c then has no bit
+// below 2^(-3p) c, which has to be at least the smallest subnormal, 2^-149
+// (2^-1074).  2^-64 (2^-512) lies well inside, and so does the reciprocal of
+// 2^64 (2^512).  Outside, an infinite bandwidth and one with an infinite
+// reciprocal among them (0 inf in the product or in the residual: NaN for every
+// pair of equal rows), the kernels' PLAIN form divides.
+template <typename T>
+__host__ inline bool div_by_holds(double c)
+{
+    const double top = sizeof(T) == 4 ? 0x1p64 : 0x1p512;
+    return c >= 1.0 / top && c <= top;
+}
+
+// exp(-s / c), r = 1 / c
+template <typename T, bool PLAIN>
+__device__ __forceinline__ T exp_quotient(T s, T c, T r)
+{
+    if constexpr (PLAIN)
+        return exp(-(s / c));
+    else
+        return exp(-div_by<T>(s, c, r));
 }
 
 // ---------------------------------------------------------------------------

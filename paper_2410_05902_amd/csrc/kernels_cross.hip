@@ -26,14 +26,15 @@ namespace mbkk {
 // K(x, y) with x held in registers.  The loop runs over all DR entries: both
 // the register row and the pool row are zero past d (DR <= padded stride), so
 // the padding adds nothing, and the fixed trip count keeps x in registers.
-template <int KIND, typename T>
+// PLAIN (FP64): see div_by_holds.
+template <int KIND, typename T, bool PLAIN>
 __device__ __forceinline__ T kfinish_direct(T s, T cneg, T param)
 {
     if constexpr (KIND == MBKK_GAUSS || KIND == MBKK_LAPLACE) {
         if constexpr (sizeof(T) == 4)
             return __builtin_amdgcn_exp2f(s * cneg);  // cneg = -log2(e) / bandwidth
         else
-            return exp(-div_by<T>(s, param, (T)1 / param));
+            return exp_quotient<T, PLAIN>(s, param, (T)1 / param);
     } else if constexpr (KIND == MBKK_LINEAR) {
         return s;
     } else {
@@ -43,7 +44,7 @@ __device__ __forceinline__ T kfinish_direct(T s, T cneg, T param)
 }
 
 // K(x_q, y) for RPL register rows at once: each coordinate of y is read once.
-template <int KIND, typename T, int DR, int RPL>
+template <int KIND, typename T, int DR, int RPL, bool PLAIN>
 __device__ __forceinline__ void kval_direct_rows(const T (&x)[RPL][DR], const float *__restrict__ y, T cneg,
                                                  T param, T (&kv)[RPL])
 {
@@ -68,10 +69,10 @@ __device__ __forceinline__ void kval_direct_rows(const T (&x)[RPL][DR], const fl
     }
 #pragma unroll
     for (int q = 0; q < RPL; ++q)
-        kv[q] = kfinish_direct<KIND, T>(s[q], cneg, param);
+        kv[q] = kfinish_direct<KIND, T, PLAIN>(s[q], cneg, param);
 }
 
-template <int KIND, typename T, int DR>
+template <int KIND, typename T, int DR, bool PLAIN>
 __device__ __forceinline__ T kval_direct(const T (&x)[DR], const float *__restrict__ y, T cneg, T param)
 {
     T s = 0;
@@ -90,7 +91,7 @@ __device__ __forceinline__ T kval_direct(const T (&x)[DR], const float *__restri
         if constexpr (sizeof(T) == 4)
             return __builtin_amdgcn_exp2f(s * cneg);  // cneg = -log2(e) / bandwidth
         else
-            return exp(-div_by<T>(s, param, (T)1 / param));
+            return exp_quotient<T, PLAIN>(s, param, (T)1 / param);
     } else if constexpr (KIND == MBKK_LINEAR) {
         return s;
     } else {
@@ -120,7 +121,7 @@ __device__ __forceinline__ double wave_bcast(double v, int e)
 // run ends where a center's segment ends.  Grid: (row tiles of 256 RPL) x (ranges).
 // ACC: the type of a run's sum (FP64 for the FP32 form's small supports, see
 // direct_min_rows).
-template <int KIND, typename T, int DR, int RPL, typename ACC>
+template <int KIND, typename T, int DR, int RPL, typename ACC, bool PLAIN>
 __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int k, int nranges, int min_rows,
                                                        const float *__restrict__ bat32,
                                                        const float *__restrict__ pool32,
@@ -188,10 +189,10 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
             const T w = wave_bcast(lw, e);
             if constexpr (DR > 0) {
                 if constexpr (RPL == 1) {
-                    acc[0] = fma((ACC)w, (ACC)kval_direct<KIND, T, DR>(x[0], y, cneg, prm), acc[0]);
+                    acc[0] = fma((ACC)w, (ACC)kval_direct<KIND, T, DR, PLAIN>(x[0], y, cneg, prm), acc[0]);
                 } else {
                     T kv[RPL];
-                    kval_direct_rows<KIND, T, DR, RPL>(x, y, cneg, prm, kv);
+                    kval_direct_rows<KIND, T, DR, RPL, PLAIN>(x, y, cneg, prm, kv);
 #pragma unroll
                     for (int q = 0; q < RPL; ++q)
                         acc[q] = fma((ACC)w, (ACC)kv[q], acc[q]);
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
                     if constexpr (sizeof(T) == 4)
                         kv = __builtin_amdgcn_exp2f(sacc * cneg);
                     else
-                        kv = exp(-div_by<T>(sacc, prm, (T)1 / prm));
+                        kv = exp_quotient<T, PLAIN>(sacc, prm, (T)1 / prm);
                 } else if constexpr (KIND == MBKK_LINEAR) {
                     kv = sacc;
                 } else {
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(256) void k_cross_direct(int nb, int d, int dp, int
             P[(int64_t)id * ldp + row[q]] = (T)acc[q];  // the last run (s0 < s1: it has entries)
 }
 
-template <int KIND, typename T>
+template <int KIND, typename T, bool PLAIN = false>
 static void dispatch_direct_width(const Layout &L, const Buffers &B, int nb, int nranges, double param, T *P,
                                   hipStream_t st)
 {
@@ -242,7 +243,7 @@ static void dispatch_direct_width(const Layout &L, const Buffers &B, int nb, int
     dim3 grid((nb + 256 * rpl - 1) / (256 * rpl), nranges);
     const int min_rows = direct_min_rows(L, nranges);
 #define MBKK_DIRECT_A(DR, RPL, ACC)                                                                               \
-    hipLaunchKernelGGL((k_cross_direct<KIND, T, DR, RPL, ACC>), grid, dim3(256), 0, st, nb, L.d, L.dp, L.k, nranges, \
+    hipLaunchKernelGGL((k_cross_direct<KIND, T, DR, RPL, ACC, PLAIN>), grid, dim3(256), 0, st, nb, L.d, L.dp, L.k, nranges, \
                        min_rows, B.bat32, B.pool32, B.sup_row, B.sup_w, B.sup_w64, B.seg_off, param, P, L.bmax)
 #define MBKK_DIRECT_R(DR, RPL)           \
     do {                                 \
@@ -276,8 +277,18 @@ void launch_cross_direct(const Layout &L, const Buffers &B, int nb, int kind, do
     if (fp64) {
         double *P = (double *)B.part;
         switch (kind) {
-        case MBKK_GAUSS: dispatch_direct_width<MBKK_GAUSS, double>(L, B, nb, nranges, param, P, st); break;
-        case MBKK_LAPLACE: dispatch_direct_width<MBKK_LAPLACE, double>(L, B, nb, nranges, param, P, st); break;
+        case MBKK_GAUSS:
+            if (div_by_holds<double>(param))
+                dispatch_direct_width<MBKK_GAUSS, double>(L, B, nb, nranges, param, P, st);
+            else
+                dispatch_direct_width<MBKK_GAUSS, double, true>(L, B, nb, nranges, param, P, st);
+            break;
+        case MBKK_LAPLACE:
+            if (div_by_holds<double>(param))
+                dispatch_direct_width<MBKK_LAPLACE, double>(L, B, nb, nranges, param, P, st);
+            else
+                dispatch_direct_width<MBKK_LAPLACE, double, true>(L, B, nb, nranges, param, P, st);
+            break;
         case MBKK_LINEAR: dispatch_direct_width<MBKK_LINEAR, double>(L, B, nb, nranges, param, P, st); break;
         default: dispatch_direct_width<MBKK_POLY2, double>(L, B, nb, nranges, param, P, st); break;
         }

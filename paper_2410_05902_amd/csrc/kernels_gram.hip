@@ -43,13 +43,12 @@ __device__ __forceinline__ void gram_term(KT &s, KT x, KT y)
     }
 }
 
-// rprm = 1 / prm, rounded.  (FP64: div_by's correction also holds for the
-// reciprocal of a double.)
-template <int KIND, typename KT>
+// rprm = 1 / prm, rounded.  PLAIN: see div_by_holds.
+template <int KIND, typename KT, bool PLAIN>
 __device__ __forceinline__ KT gram_finish(KT s, KT prm, KT rprm)
 {
     if constexpr (KIND == MBKK_GAUSS || KIND == MBKK_LAPLACE)
-        return (KT)exp(-div_by<KT>(s, prm, rprm));
+        return exp_quotient<KT, PLAIN>(s, prm, rprm);
     else if constexpr (KIND == MBKK_LINEAR)
         return s;
     else
@@ -81,7 +80,7 @@ __host__ __device__ constexpr int gram_valu_ta(int d)
 // (32 coordinates) takes 1.7 us per 1e6 pairs here.  Sums over
 // the coordinates run in the same order in both, so the kernel values are the
 // same bits.
-template <int KIND, typename KT, int DR>
+template <int KIND, typename KT, int DR, bool PLAIN>
 __global__ __launch_bounds__(kGramWG) void k_gram_rows(const GramWork A, int dp, double param,
                                                        const float *__restrict__ pool32, int zero_row)
 {
@@ -127,7 +126,7 @@ __global__ __launch_bounds__(kGramWG) void k_gram_rows(const GramWork A, int dp,
             }
 #pragma unroll
             for (int q = 0; q < RPL; ++q)
-                sum[q] += (double)gram_finish<KIND, KT>(acc[q], prm, rprm);
+                sum[q] += (double)gram_finish<KIND, KT, PLAIN>(acc[q], prm, rprm);
         }
 #pragma unroll
         for (int q = 0; q < RPL; ++q)
@@ -141,7 +140,7 @@ __global__ __launch_bounds__(kGramWG) void k_gram_rows(const GramWork A, int dp,
 // 32 / RPL coordinates at a time; the task's slot rows are read with
 // wave-uniform addresses and each coordinate serves the RPL rows.  Pairs,
 // sums and the kernel value in KT; the task sum in FP64.
-template <int KIND, typename KT>
+template <int KIND, typename KT, bool PLAIN>
 __global__ __launch_bounds__(kGramWG) void k_gram_valu(const GramWork A, int d, int dp, double param,
                                                        const float *__restrict__ pool32, int zero_row)
 {
@@ -204,7 +203,7 @@ __global__ __launch_bounds__(kGramWG) void k_gram_valu(const GramWork A, int d, 
 #pragma unroll
                 for (int i = 0; i < TA; ++i)
                     if (i < na)
-                        lsum += (double)gram_finish<KIND, KT>(acc[q][i], prm, rprm);
+                        lsum += (double)gram_finish<KIND, KT, PLAIN>(acc[q][i], prm, rprm);
             }
         }
     });
@@ -281,35 +280,47 @@ void launch_gram_plan(const Layout &L, const Buffers &B, int rr, uint32_t mask, 
                        B.goff);
 }
 
+template <int KIND, typename KT, bool PLAIN>
+static void launch_gram_valu_kind(const Layout &L, const Buffers &B, const GramWork &A, double param, hipStream_t st)
+{
+    const dim3 grid(kGramWaves / (kGramWG / 64));
+    const int zr = (int)L.PR;
+#define MBKK_GVR(DR)                                                                                              \
+    hipLaunchKernelGGL((k_gram_rows<KIND, KT, DR, PLAIN>), grid, dim3(kGramWG), 0, st, A, L.dp, param, B.pool32, zr)
+    if (L.d <= 8)
+        MBKK_GVR(8);
+    else if (L.d <= 16)
+        MBKK_GVR(16);
+    else if (L.d <= 32)
+        MBKK_GVR(32);
+    else if (L.d <= 64)
+        MBKK_GVR(64);
+    else
+        hipLaunchKernelGGL((k_gram_valu<KIND, KT, PLAIN>), grid, dim3(kGramWG), 0, st, A, L.d, L.dp, param, B.pool32, zr);
+#undef MBKK_GVR
+}
+
 template <typename KT>
 static void launch_gram_valu(const Layout &L, const Buffers &B, const GramWork &A, int kind, double param,
                              hipStream_t st)
 {
-    const dim3 grid(kGramWaves / (kGramWG / 64));
-    const int zr = (int)L.PR;
-#define MBKK_GVR(K, DR) \
-    hipLaunchKernelGGL((k_gram_rows<K, KT, DR>), grid, dim3(kGramWG), 0, st, A, L.dp, param, B.pool32, zr)
-#define MBKK_GV(K)                                                                                                  \
-    do {                                                                                                            \
-        if (L.d <= 8)                                                                                               \
-            MBKK_GVR(K, 8);                                                                                         \
-        else if (L.d <= 16)                                                                                         \
-            MBKK_GVR(K, 16);                                                                                        \
-        else if (L.d <= 32)                                                                                         \
-            MBKK_GVR(K, 32);                                                                                        \
-        else if (L.d <= 64)                                                                                         \
-            MBKK_GVR(K, 64);                                                                                        \
-        else                                                                                                        \
-            hipLaunchKernelGGL((k_gram_valu<K, KT>), grid, dim3(kGramWG), 0, st, A, L.d, L.dp, param, B.pool32, zr); \
-    } while (0)
+    const bool holds = div_by_holds<KT>(param);
     switch (kind) {
-    case MBKK_GAUSS: MBKK_GV(MBKK_GAUSS); break;
-    case MBKK_LAPLACE: MBKK_GV(MBKK_LAPLACE); break;
-    case MBKK_LINEAR: MBKK_GV(MBKK_LINEAR); break;
-    default: MBKK_GV(MBKK_POLY2); break;
+    case MBKK_GAUSS:
+        if (holds)
+            launch_gram_valu_kind<MBKK_GAUSS, KT, false>(L, B, A, param, st);
+        else
+            launch_gram_valu_kind<MBKK_GAUSS, KT, true>(L, B, A, param, st);
+        break;
+    case MBKK_LAPLACE:
+        if (holds)
+            launch_gram_valu_kind<MBKK_LAPLACE, KT, false>(L, B, A, param, st);
+        else
+            launch_gram_valu_kind<MBKK_LAPLACE, KT, true>(L, B, A, param, st);
+        break;
+    case MBKK_LINEAR: launch_gram_valu_kind<MBKK_LINEAR, KT, false>(L, B, A, param, st); break;
+    default: launch_gram_valu_kind<MBKK_POLY2, KT, false>(L, B, A, param, st); break;
     }
-#undef MBKK_GV
-#undef MBKK_GVR
 }
 
 static void launch_gram_mfma(const Layout &L, const Buffers &B, const GramWork &A, double kappa, hipStream_t st)
