@@ -51,8 +51,8 @@ struct mbkk_ctx {
     double ms_acc = 0.0;
     int64_t launches = 0;
     // pinned host copy of the device scalars and flags, written by the device
-    // (NULL: read back by a copy; always so with a static workspace, which
-    // allocates nothing)
+    // (take_mail; NULL: read back by a copy; always so with a static workspace,
+    // which allocates nothing)
     void *mail = nullptr;
     std::string err;
 };
@@ -359,6 +359,49 @@ struct Scalars {
     int32_t flags[4];
 };
 
+// Pinned host blocks for them, one per context: slots of one page, made at the
+// first need and kept until the process ends.  (A block that went with its
+// context was freed by mbkk_destroy, and hipHostFree waits for the device and
+// ends any capture under way, also when it is only a garbage collector that
+// destroys the context.)  A context that finds no slot free, or no page, reads
+// its scalars by a copy.
+constexpr size_t kMailBytes = 4096, kMailSlot = 64;
+static_assert(sizeof(Scalars) <= kMailSlot && kMailBytes / kMailSlot == 64, "a bit per slot");
+static std::mutex g_mail_mu;
+static char *g_mail_page = nullptr;
+static bool g_mail_tried = false;
+static uint64_t g_mail_used = 0;
+
+static void *take_mail()
+{
+    std::lock_guard<std::mutex> lock(g_mail_mu);
+    if (!g_mail_tried) {
+        g_mail_tried = true;
+        // (another thread's capture is not to notice the allocation)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, kMailBytes, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+            g_mail_page = (char *)p;
+        else
+            (void)hipGetLastError();
+        if (relaxed)
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (!g_mail_page || g_mail_used == ~0ull)
+        return nullptr;
+    const int slot = __builtin_ctzll(~g_mail_used);
+    g_mail_used |= 1ull << slot;
+    return g_mail_page + slot * kMailSlot;
+}
+
+// Every launch that writes the block has been waited for (read_scalars).
+static void give_mail(void *p)
+{
+    std::lock_guard<std::mutex> lock(g_mail_mu);
+    g_mail_used &= ~(1ull << (((char *)p - g_mail_page) / kMailSlot));
+}
+
 // Waits for the stream and reads them.  One read serves a call's objective and
 // its checks; the device writes them to pinned memory (a copy to pageable
 // memory, and a second one for the flags, were half of a small call's time).
@@ -366,8 +409,11 @@ static int read_scalars(mbkk_ctx *c, Scalars *s)
 {
     if (c->mail) {
         launch_report(c->B.obj, c->mail, sizeof(Scalars) / 4, c->stream);
+        void *block = c->mail;
+        c->mail = nullptr;  // not used again, nor given back, if the launch may not have ended
         HIPCHK(c, hipGetLastError());
         HIPCHK(c, hipStreamSynchronize(c->stream));
+        c->mail = block;
         memcpy(s, c->mail, sizeof(Scalars));
     } else {
         HIPCHK(c, hipMemcpyAsync(s, c->B.obj, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream));
@@ -672,7 +718,7 @@ int mbkk_destroy(mbkk_ctx *c)
         return MBKK_OK;
     }
     if (c->mail)
-        (void)hipHostFree(c->mail);
+        give_mail(c->mail);
     delete c;
     return MBKK_OK;
 }
@@ -695,10 +741,8 @@ int mbkk_set_data(mbkk_ctx *c, const float *X, int64_t ld)
     HIPCHK(c, hipStreamSynchronize(c->stream));
     // (here, where the stream is waited for anyway: a call that may be captured
     // allocates nothing)
-    if (c->device < 0 && !c->mail && hipHostMalloc(&c->mail, sizeof(Scalars), hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-        (void)hipGetLastError();
-        c->mail = nullptr;
-    }
+    if (c->device < 0 && !c->mail)
+        c->mail = take_mail();
     float f;
     memcpy(&f, &bits, sizeof(f));
     c->ymax2 = (double)f;
