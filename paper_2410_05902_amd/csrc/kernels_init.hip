@@ -389,7 +389,9 @@ __global__ __launch_bounds__(kSelThreads) void k_kpp_select(int64_t n, int64_t n
             found = p >= n ? n - 1 : p;
     } else {
         const double target = u[r] * tot;
-        if (below + inc > target)
+        // (a stretch that weighs nothing holds no crossing, though its prefix, added
+        // in another order, may come out above that of the stretch before it)
+        if (s > 0.0 && below + inc > target)
             atomicMin(&first, tid);
         __syncthreads();
         const int f = first;
@@ -406,7 +408,7 @@ __global__ __launch_bounds__(kSelThreads) void k_kpp_select(int64_t n, int64_t n
             for (int64_t c0 = q0; c0 < q1 && hitb < 0; c0 += 64) {
                 const double bv = c0 + lane < q1 ? bsum[c0 + lane] : 0.0;
                 const double bi = wave_inclusive_f64(bv);
-                const uint64_t cross = __ballot(run + bi > target);
+                const uint64_t cross = __ballot(bv > 0.0 && run + bi > target);
                 const uint64_t some = __ballot(bv > 0.0);
                 const int at = cross ? __ffsll((unsigned long long)cross) - 1
                                      : (some ? 63 - __clzll((long long)some) : -1);
