@@ -531,8 +531,8 @@ void launch_kpp_round(const Layout &L, const Buffers &B, int r, int kind, double
         }
 #undef MBKK_KUPD
     }
-    // the thresholds' array is scratch here: the self norms at a bandwidth are
-    // made anew after any seeding
+    // the thresholds' array is scratch here (mbkk_init_kmeanspp drops the self
+    // norms at a bandwidth that it may hold)
     const bool prune = (kind == MBKK_GAUSS || kind == MBKK_LAPLACE) && r > 0 && r + 1 < L.k;
     const dim3 grid(prune ? (unsigned)((r + kSelThreads / 16 - 1) / (kSelThreads / 16)) : 1u);
 #define MBKK_KSEL(K, PR)                                                                                          \

@@ -805,6 +805,8 @@ int mbkk_init_kmeanspp(mbkk_ctx *c, const double *u_host, int32_t *idx_out_dev)
     for (int r = 0; r < L.k; ++r)
         if (!(u_host[r] >= 0.0 && u_host[r] < 1.0))
             return fail(c, MBKK_E_INVALID, "uniforms must lie in [0, 1)");
+    // the rounds' thresholds go to the array of the self norms at a bandwidth
+    c->sig_version = -1;
     HIPCHK(c, hipMemcpyAsync(c->B.u, u_host, sizeof(double) * L.k, hipMemcpyHostToDevice, c->stream));
     launch_kpp_self(L, c->B, c->cfg.kernel, c->cfg.kernel_param, c->stream);
     for (int r = 0; r < L.k; ++r)
