@@ -8,14 +8,15 @@
 // loads, and where a center has collapsed (a candidate of 10^4 entries) the
 // FP64 rate of the compute units at work on it.  So a row of little work is
 // done by the scoring workgroup that found it (kernels_score.hip), all 16 waves
-// together (3 us a row); a row of much work is listed and split over up to 16
-// workgroups of a later launch: the update's own where the small one runs
-// (kernels_prep.hip), else a launch of k_rescore.  That launch's chain is 20 us
-// long, but it is the same for 1 and for 30 rows.  (In the scoring kernel with
-// one wave per row and a lane per entry, a launch that re-scored any row took
-// 35 us more, and up to 900 us with a collapsed center; 1M x 128, k = 100,
-// b = 4096.)  An entry's row is read by 16 lanes (whole 256-byte stretches),
-// and one exp serves 64 entries.
+// together (3 us a row); a row of much work is listed for a later launch, the
+// update's own where the small one runs (kernels_prep.hip), else k_rescore, and
+// split over up to 16 of its workgroups.  (At most as many centers as the launch
+// has threads per workgroup, 512 in k_rescore: with more, a listed row is one
+// workgroup's.)  That launch's chain is 20 us long, but it is the same for 1 and
+// for 30 rows.  (In the scoring kernel with one wave per row and a lane per entry,
+// a launch that re-scored any row took 35 us more, and up to 900 us with a
+// collapsed center; 1M x 128, k = 100, b = 4096.)  An entry's row is read by 16
+// lanes (whole 256-byte stretches), and one exp serves 64 entries.
 #pragma once
 
 #include "cross_layout.h"
@@ -241,7 +242,7 @@ __device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreL
         if (cand)
             S.cand[at + __popcll(m & ((1ull << lane) - 1ull))] = jl;
         __syncthreads();
-        const bool split = !SCORING && pl > 0 && np == 1 && nc <= kRescoreMaxCand;
+        const bool split = !SCORING && pl > 0 && nc <= kRescoreMaxCand;  // (pl > 0: one pass)
         if (SCORING && A.split && nc <= kRescoreMaxCand) {
             int ne = 0;
             for (int i = 0; i < nc; ++i)
@@ -374,8 +375,10 @@ __device__ __forceinline__ bool rescore_listed(const RescoreArgs &A, int nrows)
     __shared__ int s_cnt[kRescoreMaxWaves];
     if (nrows == 0)
         return blockIdx.x == 0;
+    // (a row whose centers take the workgroup several passes is not split: its
+    // parts would look for the candidates and return)
     int pl = 0;
-    while (A.split && (2 << pl) <= kRescoreMaxParts && (nrows << (pl + 1)) <= (int)gridDim.x)
+    while (A.split && A.k <= (int)blockDim.x && (2 << pl) <= kRescoreMaxParts && (nrows << (pl + 1)) <= (int)gridDim.x)
         ++pl;
     // workgroups with no row don't arrive (their counts on one address take
     // their turns: 256 of them 5 us)
