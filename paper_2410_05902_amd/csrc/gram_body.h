@@ -259,14 +259,20 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
             for (int r = 0; r < NR; ++r)
                 load_rows(ra_w[r], av[r]);
         }
+        // slot row n's norm for the output rows m, once per task
+        auto publish_norms = [&]() {
+            if (g == 0) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    sqa[wl][r][n] = c1 * sqa_v[r];
+            }
+        };
         // lane: column n (column row), rows m = 4 g + i (slot rows); the
         // row norms were written by this wave (in-order LDS access) and are
         // read as one 16-byte load; rows past the cluster add an exact 0 (the
         // sum is positive, so no sign of zero changes)
         auto tile_sum = [&](int tile, int r, const f32x4 &acc, float sqe_v) {
             const int qe_t = tile * 16 + n;
-            if (tile == tile0 && g == 0)
-                sqa[wl][r][n] = c1 * sqa_v[r];  // slot row n's norm for the output rows m, once per task
             const float se_ = c1 * sqe_v;
             if (qe_t < ec.n) {
                 const f32x4 sq4 = *(const f32x4 *)&sqa[wl][r][4 * g];
@@ -299,6 +305,10 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
             pass_rows(av[0], av[0]);
             if (two)  // wave uniform
                 pass_rows(av[NR - 1], av[NR - 1]);
+            // (loaded ahead of the rows just waited for; kept in registers to the
+            // first tile's sums, two registers were spilled at 128 coordinates, 12.1 us
+            // a balanced step against 11.6 us so)
+            publish_norms();
 #pragma unroll
             for (int t = 0; t < QX; ++t) {
                 const int tile = tile0 + t;
@@ -310,12 +320,6 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                 f32x4 ev[NS];
                 pass_rows(en, ev);
                 load_rows(rn, en);
-                // the slot row's norm is needed by this point (the products
-                // wait for the row loads anyway), so its load is not sunk into
-                // the branch that publishes it
-#pragma unroll
-                for (int r = 0; r < NR; ++r)
-                    asm volatile("" ::"v"(sqa_v[r]));
                 f32x4 acc[NR];
 #pragma unroll
                 for (int r = 0; r < NR; ++r)
@@ -395,6 +399,8 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                         v[h] = *(const f32x4 *)(src[h] + 32 * c0);
                     take(v);
                 }
+                if (tile == tile0)
+                    publish_norms();
                 tile_sum(tile, 0, acc, sqe_v);
             }
         }
