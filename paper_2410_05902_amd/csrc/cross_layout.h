@@ -84,31 +84,20 @@ inline int bs_nranges(int nb, int mode, int dp)
     return r < 1 ? 1 : r;
 }
 
-// LAYOUT 0: the direct kernel's runs (ranges of RR rows): run j (the run at
-// the center's first row) plus run k + r of every range r that starts
-// strictly inside the center's segment.
-// LAYOUT 1: the MFMA kernels write one partial per run of a center's blocks
-// inside a range of RB blocks, at the run's first block: the center's first
-// block and every range start inside the center.
+// A center's cross term from the partials of the MFMA kernels, summed in FP32.
+// LAYOUT 1: one partial per run of a center's blocks inside a range of RB
+// blocks, at the run's first block: the center's first block and every range
+// start inside the center.
 // LAYOUT 2 (packed segments, which may start inside a block): two slots per
 // block, 2 b for the run from block b's first row (a range start, or a center
 // starting there) and 2 b + 1 for a center starting inside block b; a
 // center's partials are its first slot and slot 2 b of every range start b
 // after its first block and inside its segment.
-// The direct kernel's runs are summed in FP64, the MFMA kernels' in FP32.
 template <typename T, int LAYOUT>
 __device__ __forceinline__ double cross_of(const T *__restrict__ part, int ldp, int row, int j,
-                                           const int32_t *__restrict__ seg_off, int RB, int k = 0)
+                                           const int32_t *__restrict__ seg_off, int RB)
 {
-    if constexpr (LAYOUT == 0) {
-        const int s0 = seg_off[j], s1 = seg_off[j + 1];
-        if (s0 >= s1)
-            return 0.0;
-        double s = (double)part[(int64_t)j * ldp + row];
-        for (int r = s0 / RB + 1; r * RB < s1; ++r)
-            s += (double)part[(int64_t)(k + r) * ldp + row];
-        return s;
-    } else if constexpr (LAYOUT == 1) {
+    if constexpr (LAYOUT == 1) {
         const int bs = seg_off[j] / 32, be = seg_off[j + 1] / 32;
         if (bs >= be)
             return 0.0;

@@ -15,8 +15,10 @@
 //          ranges form a monotone staircase, so w + jc is distinct per run;
 //   fold : per live (j, c), the partials of its waves in wave order.
 // Every sum has a fixed order, so the blocks are bit-reproducible.
-//   k_gram_valu : any kernel, FP32 or FP64 arithmetic; a task is 8 to 32 slot
-//                 rows (wave-uniform) x 64 column rows (one per lane);
+//   k_gram_rows : any kernel, FP32 or FP64 arithmetic, up to 64 coordinates; a
+//                 task is 8 to 32 slot rows (wave-uniform) x 64 or 128 column
+//                 rows (one or two per lane, in registers);
+//   k_gram_valu : the same past 64 coordinates, 16 or 32 slot rows;
 //   k_gram_mfma : Gaussian MFMA forms; FP32 MFMA products and exp fused in
 //                 registers; a task is output blocks of 16 x 16.  The BF16
 //                 forms take their Gram blocks here too: the self norms keep
@@ -82,7 +84,7 @@ __host__ __device__ constexpr int gram_valu_ta(int d)
 // same bits.
 template <int KIND, typename KT, int DR, bool PLAIN>
 __global__ __launch_bounds__(kGramWG) void k_gram_rows(const GramWork A, int dp, double param,
-                                                       const float *__restrict__ pool32, int zero_row)
+                                                       const float *__restrict__ pool32)
 {
     constexpr int RPL = gram_valu_rpl<KT>(), TA = gram_valu_ta<KT>(DR);
     const int lane = threadIdx.x & 63;
@@ -284,9 +286,8 @@ template <int KIND, typename KT, bool PLAIN>
 static void launch_gram_valu_kind(const Layout &L, const Buffers &B, const GramWork &A, double param, hipStream_t st)
 {
     const dim3 grid(kGramWaves / (kGramWG / 64));
-    const int zr = (int)L.PR;
-#define MBKK_GVR(DR)                                                                                              \
-    hipLaunchKernelGGL((k_gram_rows<KIND, KT, DR, PLAIN>), grid, dim3(kGramWG), 0, st, A, L.dp, param, B.pool32, zr)
+#define MBKK_GVR(DR)                                                                                          \
+    hipLaunchKernelGGL((k_gram_rows<KIND, KT, DR, PLAIN>), grid, dim3(kGramWG), 0, st, A, L.dp, param, B.pool32)
     if (L.d <= 8)
         MBKK_GVR(8);
     else if (L.d <= 16)
@@ -296,7 +297,8 @@ static void launch_gram_valu_kind(const Layout &L, const Buffers &B, const GramW
     else if (L.d <= 64)
         MBKK_GVR(64);
     else
-        hipLaunchKernelGGL((k_gram_valu<KIND, KT, PLAIN>), grid, dim3(kGramWG), 0, st, A, L.d, L.dp, param, B.pool32, zr);
+        hipLaunchKernelGGL((k_gram_valu<KIND, KT, PLAIN>), grid, dim3(kGramWG), 0, st, A, L.d, L.dp, param,
+                           B.pool32, (int)L.PR);
 #undef MBKK_GVR
 }
 

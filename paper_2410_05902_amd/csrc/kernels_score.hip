@@ -435,7 +435,7 @@ double selfnorm_error_bound(int dp, double ymax2, double kappa)
 }
 
 // The list lies in the differentiation form's per-row arrays (gr_perm, rowds),
-// the split rows' scratch in the seeding's (D2: at most 512 (row, part) pairs
+// the split rows' scratch in the seeding's (D2: at most 256 (row, part) pairs
 // of 16 sums, kself: at most 128 records): nothing else uses them between a
 // scoring pass and the launch that finishes its rows.  Data of less than 8192
 // rows has no room there and lists no row.
@@ -460,7 +460,7 @@ RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precisio
     R.list = B.gr_perm;
     R.delta = B.rowds;
     R.ctr = B.rs_ctr;
-    static_assert(2 * kRescoreWGs * kRescoreMaxCand * 8 <= 8 * 8192 &&
+    static_assert(kRescoreWGs * kRescoreMaxCand * 8 <= 8 * 8192 &&
                       sizeof(RescoreRec) * (kRescoreWGs / 2) <= 8 * 8192,
                   "the split rows' sums and records fit in the scratch of 8192 rows");
     R.split = L.n >= 8192;
