@@ -523,8 +523,9 @@ __global__ __launch_bounds__(kDpTableWG) void k_dp_table(int64_t n, int d, int64
 // workgroup) and runs over all grouped entries, staged 64 at a time through
 // LDS (double-buffered; rows padded by 16 bytes so that the 16-byte reads of
 // 16 lanes fall in distinct banks).  After each 32-entry tile the lane sums
-// its kernel values per center segment (masks on i); at the end of a segment
-// the two lane halves are combined (permlane32 swap) and
+// its kernel values per center segment, in one pass over them (`segments`
+// below); at the end of a segment the two lane halves are combined (permlane32
+// swap), unless it lies in one of them, and
 //     S[j][x] = (alpha_j / b_j) sum_{y in B^j} K(x, y)
 // is stored; k_dp_blend then forms T <- (1 - alpha) T + S for the touched
 // centers (200 us at 1M points, k = 100; reading T here at every segment's end

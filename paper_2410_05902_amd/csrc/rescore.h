@@ -76,7 +76,14 @@ struct RescoreArgs {
 };
 
 // Stores that workgroups of other XCDs read in the same launch: agent scope,
-// through the XCD's L2.
+// through the XCD's L2.  What workgroups hand over in a launch is ordered by
+// these, by each wave's wait for its stores before its workgroup arrives at
+// ctr[1], and by nothing else: no release or acquire.  So labels, mind and
+// margin of listed rows, rec, psum and ctr[1] are accessed with store_agent,
+// load_agent and atomics only, until the last workgroup to arrive has written
+// the listed rows again (write_row) and may read them plainly; Dout and the
+// caller's arrays are not read in the launch, and the list, its thresholds, the
+// partials and the centers' arrays come from earlier launches.
 template <typename T>
 __device__ __forceinline__ void store_agent(T *p, T v)
 {

@@ -15,8 +15,8 @@ from tests._parity import dist_rel_err, oracle_state_to_gpu
 pytestmark = pytest.mark.gpu
 
 
-# n sets the room (n / 8 jobs of 128 entries): 1000 rows list none, 3000 some,
-# 40000 all; d = 160 takes the other cross kernel, k = 600 the general update
+# rows are listed from n = 8192 on (none at 1000 and 3000); d = 160 takes the other
+# cross kernel, k = 600 the general update (test_gpu_rescore_split.py: the rules' edges)
 @pytest.mark.parametrize("n,d,k,b", [(1000, 64, 5, 700), (3000, 64, 5, 1000), (40000, 128, 5, 1025),
                                      (40000, 160, 4, 640), (40000, 64, 600, 900), (60000, 32, 1100, 800)])
 def test_listed_rows(n, d, k, b):
