@@ -49,10 +49,14 @@ inline int direct_nranges(int nb, int d, bool fp64)
 }
 
 // Fewest entries per range: kDirectMinRows where the fullest support has no
-// more per range anyway (so that every larger one keeps its cut), else 1.
+// more per range anyway (so that every larger one keeps its cut), else 1; also
+// 1 past 64 coordinates, where a lane reads its batch row again for every
+// entry and the cross kernel needs the workgroups (Laplacian, b = 64, 784
+// coordinates: 78 us in ranges of one entry, 549 us of 8; 100 coordinates, b = 256:
+// 51 and 104 us).
 inline int direct_min_rows(const Layout &L, int nranges)
 {
-    return (L.Mcap + nranges - 1) / nranges <= kDirectMinRows ? kDirectMinRows : 1;
+    return L.d <= 64 && (L.Mcap + nranges - 1) / nranges <= kDirectMinRows ? kDirectMinRows : 1;
 }
 
 constexpr int kBsStageBlocks = 4;  // support blocks (32 rows) per stage of the MFMA kernel

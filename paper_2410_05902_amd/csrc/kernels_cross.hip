@@ -264,7 +264,7 @@ static void dispatch_direct_width(const Layout &L, const Buffers &B, int nb, int
     else if (L.d <= 64)
         MBKK_DIRECT(64);
     else
-        MBKK_DIRECT(0);
+        MBKK_DIRECT_A(0, 1, T);  // (direct_min_rows is 1)
 #undef MBKK_DIRECT
 #undef MBKK_DIRECT_R
 #undef MBKK_DIRECT_A
