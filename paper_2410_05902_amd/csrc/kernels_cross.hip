@@ -311,17 +311,21 @@ void launch_cross_direct(const Layout &L, const Buffers &B, int nb, int kind, do
 // weighted sum over the support is then an in-lane reduction plus one
 // exchange between the two lane halves.
 //
-// Workgroup tile: 128 support rows x 64 batch rows, 4 waves in a 2x2 grid,
-// each wave 64 x 32 = 2 MFMA blocks of 32 x 32; K staged through LDS in chunks
-// of 32 (one LDS buffer, next chunk prefetched into registers), four
-// workgroups per compute unit.  What bounds it is the matrix core, and the
-// last round of tiles: with 128 x 128 tiles, two workgroups per unit, b = 1024
-// rows against 8192 entries are 536 tiles for 512 places, and the second round
-// held 24 of them (164 us in FP32 at 784 coordinates; 115 us with these
-// tiles, which are half a round's worth each).  Segments are padded to
-// multiples of 32 rows so that every 32-row block belongs to one center.
-// Output: one partial per (32-row block, batch row); the two blocks of a wave
-// are merged when they belong to the same center.
+// Workgroup tile: 128 support rows x TB batch rows, 4 waves in a 2x2 grid,
+// each wave 64 x TB / 2 = 2 x TB / 64 MFMA blocks of 32 x 32; K staged through
+// LDS in chunks of 32 (one LDS buffer, next chunk prefetched into registers).
+// What bounds it is the matrix core, the rows' way to it, and the last round of
+// tiles.  TB = 64 (four workgroups per compute unit) fills the chip where there
+// are few tiles: b = 1024 rows against 8192 entries are 536 tiles of 128 x 128 for
+// 512 places, and the second round held 24 of them (164 us in FP32 at 784
+// coordinates, 115 us at TB = 64).  TB = 128 (two) reads each support row half as
+// often: in FP32 960 -> 903 us (784 coordinates, b = 4096, 16k entries), in BF16,
+// whose products take an eighth of the time, 591 -> 480 us (three products, 256
+// coordinates, b = 8192, 33k entries) and 265 -> 212 us (one).  The choice:
+// cross_mfma_tile.  Segments are padded to multiples of 32 rows so that every
+// 32-row block belongs to one center.  Output: one partial per (32-row block,
+// batch row); the two blocks of a wave are merged when they belong to the same
+// center.
 //   MODE 0: FP32 MFMA 32x32x2 (plain form)
 //   MODE 1: BF16 32x32x16, hi.hi + hi.lo + lo.hi (compensated split)
 //   MODE 2: BF16 32x32x16, hi.hi only
@@ -346,15 +350,16 @@ struct CrossArgs {
     int ldp;
 };
 
-constexpr int TS = 128, TB = 64, KC = 32;
+constexpr int TS = 128, KC = 32;
 constexpr int LDF = KC + 4;  // FP32 LDS row stride (floats): 144 B, conflict-free b128 reads
 constexpr int LDH = KC + 8;  // BF16 LDS row stride (elements): 80 B
 
-template <int MODE>
-__global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
+template <int MODE, int TB>
+__global__ __launch_bounds__(256, TB == 64 ? 4 : 2) void k_cross_mfma(const CrossArgs A)
 {
     constexpr bool F32 = MODE == 0;
     constexpr bool X3 = MODE == 1;
+    constexpr int NB = TB / 64;  // 32-row blocks of the batch per wave
     // LDS (one buffer; the next K chunk is prefetched into registers):
     // FP32 -> As, Bs [TS][LDF] floats; BF16 -> hi (and lo) [TS][LDH] each
     constexpr int LDS_F = F32 ? (TS + TB) * LDF : 4;
@@ -389,19 +394,21 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
     }
 
     const int nK = A.dp / KC;
-    f32x16 acc[2];
+    f32x16 acc[2][NB];
 #pragma unroll
     for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            acc[a][i] = 0.0f;
+        for (int bb = 0; bb < NB; ++bb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                acc[a][bb][i] = 0.0f;
 
     if constexpr (F32) {
-        // loader: 4 rows of A and 2 of B per thread, one float4 each
+        // loader: 4 rows of A and 2 NB of B per thread, one float4 each
         const int lr = tid >> 3, lc = (tid & 7) * 4;
         const float *asrc[4];
-        const float *bsrc[2];
-        bool bok[2];
+        const float *bsrc[2 * NB];
+        bool bok[2 * NB];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int s = s0 + lr + 32 * q;
@@ -409,18 +416,18 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
             asrc[q] = A.pool32 + prow * A.dp + lc;
         }
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
+        for (int q = 0; q < 2 * NB; ++q) {
             const int r = lr + 32 * q;
             bok[q] = b0 + r < A.nb;
             bsrc[q] = A.bat32 + (int64_t)(bok[q] ? b0 + r : 0) * A.dp + lc;
         }
-        f32x4 ra[4], rb[2];
+        f32x4 ra[4], rb[2 * NB];
         auto gload = [&](int kc) {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 ra[q] = *(const f32x4 *)(asrc[q] + kc * KC);
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
+            for (int q = 0; q < 2 * NB; ++q)
                 rb[q] = bok[q] ? *(const f32x4 *)(bsrc[q] + kc * KC) : f32x4{0, 0, 0, 0};
         };
         auto lstore = [&]() {
@@ -430,7 +437,7 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
             for (int q = 0; q < 4; ++q)
                 *(f32x4 *)(As + (lr + 32 * q) * LDF + lc) = ra[q];
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
+            for (int q = 0; q < 2 * NB; ++q)
                 *(f32x4 *)(Bs + (lr + 32 * q) * LDF + lc) = rb[q];
         };
         gload(0);
@@ -443,21 +450,25 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
             const float *As = smf;
             const float *Bs = As + TS * LDF;
             // K permutation inside the chunk: MFMA step s, lane half h -> column h*16 + s
-            f32x4 af[2][4], bf[4];
+            f32x4 af[2][4], bf[NB][4];
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     af[a][v] = *(const f32x4 *)(As + (wm * 64 + a * 32 + frow) * LDF + fh * 16 + v * 4);
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                bf[v] = *(const f32x4 *)(Bs + (wn * 32 + frow) * LDF + fh * 16 + v * 4);
+            for (int bb = 0; bb < NB; ++bb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    bf[bb][v] = *(const f32x4 *)(Bs + ((wn * NB + bb) * 32 + frow) * LDF + fh * 16 + v * 4);
 #pragma unroll
             for (int s = 0; s < 16; ++s)
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
-                    acc[a] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[a][s >> 2][s & 3], bf[s >> 2][s & 3], acc[a], 0, 0,
-                                                                  0);
+#pragma unroll
+                    for (int bb = 0; bb < NB; ++bb)
+                        acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[a][s >> 2][s & 3], bf[bb][s >> 2][s & 3],
+                                                                           acc[a][bb], 0, 0, 0);
             if (kc + 1 < nK) {
                 __syncthreads();
                 lstore();
@@ -465,7 +476,7 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
             }
         }
     } else {
-        // loader: 2 rows of A and one of B per thread, 8 bf16 (16 B) each, hi and lo
+        // loader: 2 rows of A and NB of B per thread, 8 bf16 (16 B) each, hi and lo
         const int lr = tid >> 2, lc = (tid & 3) * 8;
         const uint16_t *ahs[2], *als[2];
 #pragma unroll
@@ -475,10 +486,17 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
             ahs[q] = A.poolhi + prow * A.dp + lc;
             als[q] = A.poollo + prow * A.dp + lc;
         }
-        const bool bok = b0 + lr < A.nb;
-        const int64_t brow = bok ? b0 + lr : 0;
-        const uint16_t *bhs = A.bathi + brow * A.dp + lc, *bls = A.batlo + brow * A.dp + lc;
-        u16x8 rah[2], ral[2], rbh, rbl;
+        const uint16_t *bhs[NB], *bls[NB];
+        bool bok[NB];
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const int r = lr + 64 * q;
+            bok[q] = b0 + r < A.nb;
+            const int64_t brow = bok[q] ? b0 + r : 0;
+            bhs[q] = A.bathi + brow * A.dp + lc;
+            bls[q] = A.batlo + brow * A.dp + lc;
+        }
+        u16x8 rah[2], ral[2], rbh[NB], rbl[NB];
         const u16x8 z8 = {0, 0, 0, 0, 0, 0, 0, 0};
         auto gload = [&](int kc) {
 #pragma unroll
@@ -487,9 +505,12 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
                 if constexpr (X3)
                     ral[q] = *(const u16x8 *)(als[q] + kc * KC);
             }
-            rbh = bok ? *(const u16x8 *)(bhs + kc * KC) : z8;
-            if constexpr (X3)
-                rbl = bok ? *(const u16x8 *)(bls + kc * KC) : z8;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                rbh[q] = bok[q] ? *(const u16x8 *)(bhs[q] + kc * KC) : z8;
+                if constexpr (X3)
+                    rbl[q] = bok[q] ? *(const u16x8 *)(bls[q] + kc * KC) : z8;
+            }
         };
         auto lstore = [&]() {
 #pragma unroll
@@ -499,9 +520,13 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
                 if constexpr (X3)
                     *(u16x8 *)(sAl + off) = ral[q];
             }
-            *(u16x8 *)(sBh + lr * LDH + lc) = rbh;
-            if constexpr (X3)
-                *(u16x8 *)(sBl + lr * LDH + lc) = rbl;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const int off = (lr + 64 * q) * LDH + lc;
+                *(u16x8 *)(sBh + off) = rbh[q];
+                if constexpr (X3)
+                    *(u16x8 *)(sBl + off) = rbl[q];
+            }
         };
         gload(0);
         lstore();
@@ -512,7 +537,7 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
                 gload(kc + 1);
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                bf16x8 ah[2], al[2], bh, bl;
+                bf16x8 ah[2], al[2], bh[NB], bl[NB];
 #pragma unroll
                 for (int a = 0; a < 2; ++a) {
                     const int off = (wm * 64 + a * 32 + frow) * LDH + s * 16 + fh * 8;
@@ -520,18 +545,23 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
                     if constexpr (X3)
                         al[a] = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sAl + off));
                 }
-                const int boff = (wn * 32 + frow) * LDH + s * 16 + fh * 8;
-                bh = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sBh + boff));
-                if constexpr (X3)
-                    bl = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sBl + boff));
 #pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh, acc[a], 0, 0, 0);
-                    if constexpr (X3) {
-                        acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl, acc[a], 0, 0, 0);
-                        acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh, acc[a], 0, 0, 0);
-                    }
+                for (int bb = 0; bb < NB; ++bb) {
+                    const int off = ((wn * NB + bb) * 32 + frow) * LDH + s * 16 + fh * 8;
+                    bh[bb] = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sBh + off));
+                    if constexpr (X3)
+                        bl[bb] = __builtin_bit_cast(bf16x8, *(const u16x8 *)(sBl + off));
                 }
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int bb = 0; bb < NB; ++bb) {
+                        acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bh[bb], acc[a][bb], 0, 0, 0);
+                        if constexpr (X3) {
+                            acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[a], bl[bb], acc[a][bb], 0, 0, 0);
+                            acc[a][bb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[a], bh[bb], acc[a][bb], 0, 0, 0);
+                        }
+                    }
             }
             if (kc + 1 < nK) {
                 __syncthreads();
@@ -545,39 +575,48 @@ __global__ __launch_bounds__(256, 4) void k_cross_mfma(const CrossArgs A)
     // and support rows m = 8 (i / 4) + 4 (l / 32) + i % 4, i = 0..15.
     const int n = lane & 31, h = lane >> 5;
     const int Mb = M / 32;
-    float tot[2];
-    const int col = b0 + wn * 32 + n;
-    const float ax = col < A.nb ? A.c1 * A.batsq[col] : 0.0f;
+    float tot[2][NB];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const int mbase = wm * 64 + a * 32;
-        float sum = 0.0f;
+    for (int bb = 0; bb < NB; ++bb) {
+        const int col = b0 + (wn * NB + bb) * 32 + n;
+        const float ax = col < A.nb ? A.c1 * A.batsq[col] : 0.0f;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            const int m0 = mbase + 8 * g + 4 * h;
-            const f32x4 ay = *(const f32x4 *)(sAy + m0);
-            const f32x4 w = *(const f32x4 *)(sW + m0);
+        for (int a = 0; a < 2; ++a) {
+            const int mbase = wm * 64 + a * 32;
+            float sum = 0.0f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float arg = fmaf(acc[a][4 * g + q], A.c2, ax + ay[q]);
-                sum = fmaf(w[q], __builtin_amdgcn_exp2f(arg), sum);
+            for (int g = 0; g < 4; ++g) {
+                const int m0 = mbase + 8 * g + 4 * h;
+                const f32x4 ay = *(const f32x4 *)(sAy + m0);
+                const f32x4 w = *(const f32x4 *)(sW + m0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float arg = fmaf(acc[a][bb][4 * g + q], A.c2, ax + ay[q]);
+                    sum = fmaf(w[q], __builtin_amdgcn_exp2f(arg), sum);
+                }
             }
+            sum += __shfl_xor(sum, 32);
+            tot[a][bb] = sum;
         }
-        sum += __shfl_xor(sum, 32);
-        tot[a] = sum;
     }
     const int blk0 = (s0 + wm * 64) / 32;
     if (blk0 >= Mb)
         return;
     const bool has1 = blk0 + 1 < Mb;
     const bool merge = has1 && A.blk_center[blk0] == A.blk_center[blk0 + 1];
-    if (h == 0 && col < A.nb) {
-        if (merge) {
-            A.part[(int64_t)blk0 * A.ldp + col] = tot[0] + tot[1];
-        } else {
-            A.part[(int64_t)blk0 * A.ldp + col] = tot[0];
-            if (has1)
-                A.part[(int64_t)(blk0 + 1) * A.ldp + col] = tot[1];
+    if (h == 0) {
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) {
+            const int col = b0 + (wn * NB + bb) * 32 + n;
+            if (col >= A.nb)
+                continue;
+            if (merge) {
+                A.part[(int64_t)blk0 * A.ldp + col] = tot[0][bb] + tot[1][bb];
+            } else {
+                A.part[(int64_t)blk0 * A.ldp + col] = tot[0][bb];
+                if (has1)
+                    A.part[(int64_t)(blk0 + 1) * A.ldp + col] = tot[1][bb];
+            }
         }
     }
 }
@@ -1172,6 +1211,17 @@ __global__ __launch_bounds__(256 * bs_wps(MODE, DP), kBsOcc) void k_cross_bs(con
 #endif
 }
 
+// Batch rows of a tile of the general MFMA cross kernel (the tiles' measures are
+// beside the kernel): 128 where a full support has enough such tiles, a round of
+// two per compute unit in BF16, four rounds in FP32.  Both tiles are equal at
+// 1632 tiles in FP32, the larger one is 2 to 6 % faster from 2130 on; in BF16 it is
+// 5 to 10 % slower at 300 tiles and 5 to 10 % faster at 536.
+static int cross_mfma_tile(const Layout &L, int nb, int precision)
+{
+    const int64_t tiles = L.Mcap / TS * ((nb + 127) / 128);
+    return tiles >= (precision == MBKK_FP32 ? 2048 : 512) ? 128 : 64;
+}
+
 void launch_cross_mfma(const Layout &L, const Buffers &B, int nb, int precision, double kappa, hipStream_t st)
 {
     const double l2e = 1.4426950408889634;
@@ -1223,7 +1273,8 @@ void launch_cross_mfma(const Layout &L, const Buffers &B, int nb, int precision,
     CrossArgs A;
     A.nb = nb;
     A.dp = L.dp;
-    A.ntB = (nb + TB - 1) / TB;
+    const int tb = cross_mfma_tile(L, nb, precision);
+    A.ntB = (nb + tb - 1) / tb;
     const int64_t ntiles = L.Mcap / TS * A.ntB;  // of a full support
     A.zero_row = L.PR;
     A.seg_total = B.seg_off + L.k;
@@ -1243,12 +1294,20 @@ void launch_cross_mfma(const Layout &L, const Buffers &B, int nb, int precision,
     A.part = (float *)B.part;
     A.ldp = L.bmax;
     const int64_t grid = (ntiles + 7) / 8 * 8;
+#define MBKK_CM(MODE)                                                                            \
+    do {                                                                                         \
+        if (tb == 64)                                                                            \
+            hipLaunchKernelGGL((k_cross_mfma<MODE, 64>), dim3((unsigned)grid), dim3(256), 0, st, A);  \
+        else                                                                                     \
+            hipLaunchKernelGGL((k_cross_mfma<MODE, 128>), dim3((unsigned)grid), dim3(256), 0, st, A); \
+    } while (0)
     if (precision == MBKK_FP32)
-        hipLaunchKernelGGL(k_cross_mfma<0>, dim3((unsigned)grid), dim3(256), 0, st, A);
+        MBKK_CM(0);
     else if (precision == MBKK_BF16X3)
-        hipLaunchKernelGGL(k_cross_mfma<1>, dim3((unsigned)grid), dim3(256), 0, st, A);
+        MBKK_CM(1);
     else
-        hipLaunchKernelGGL(k_cross_mfma<2>, dim3((unsigned)grid), dim3(256), 0, st, A);
+        MBKK_CM(2);
+#undef MBKK_CM
 }
 
 }  // namespace mbkk
