@@ -33,17 +33,24 @@ inline int direct_rpl(int d, bool fp64) { return !fp64 && d <= 32 ? 2 : 1; }
 // (one round at 8 waves per SIMD), 3/4 of that with two rows per lane (whose
 // registers allow 6 waves per SIMD).  In FP64 a row of 33 to 64 coordinates
 // takes 168 registers, 3 waves per SIMD, one of 17 to 32 takes 106, 4 waves: one
-// round of workgroups that start with long ranges there (b = 1024, M = 4096,
+// round of workgroups there while the ranges are short (b = 1024, M = 4096,
 // d = 64: nine entries per range, behind a start of two load round trips, took
-// 99 us; 22 entries take 63 us).
-inline int direct_nranges(int nb, int d, bool fp64)
+// 99 us; 22 entries take 63 us), and kDirectWGs again from 128 entries of a full
+// support per range on, where the starts weigh less than what the last workgroups
+// keep waiting (d = 64, one round against kDirectWGs: M = 8242, b = 2048, 86 entries
+// 174 and 184 us; M = 12308, b = 2048, 129 entries 260 and 261 us; M = 16404,
+// b = 4096, 342 entries 618 and 572 us; d = 32: 64 entries 96 and 97 us, 128
+// entries 170 and 162 us).
+inline int direct_nranges(const Layout &L, int nb, bool fp64)
 {
-    const int rpl = direct_rpl(d, fp64);
+    const int rpl = direct_rpl(L.d, fp64);
     const int tiles = (nb + 256 * rpl - 1) / (256 * rpl);
-    const int wgs = rpl == 2                          ? kDirectWGs * 3 / 4
-                    : fp64 && d > 32 && d <= 64       ? kDirectWGs * 3 / 8
-                    : fp64 && d > 16 && d <= 32       ? kDirectWGs / 2
-                                                      : kDirectWGs;
+    int wgs = rpl == 2 ? kDirectWGs * 3 / 4 : kDirectWGs;
+    if (fp64 && L.d > 16 && L.d <= 64) {
+        const int one = L.d > 32 ? kDirectWGs * 3 / 8 : kDirectWGs / 2;
+        if (L.Mcap * tiles / one < 128)
+            wgs = one;
+    }
     const int r = wgs / tiles;
     return r < 1 ? 1 : r;
 }

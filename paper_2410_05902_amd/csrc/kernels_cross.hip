@@ -273,7 +273,7 @@ static void dispatch_direct_width(const Layout &L, const Buffers &B, int nb, int
 void launch_cross_direct(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64,
                          hipStream_t st)
 {
-    const int nranges = direct_nranges(nb, L.d, fp64);
+    const int nranges = direct_nranges(L, nb, fp64);
     if (fp64) {
         double *P = (double *)B.part;
         switch (kind) {

@@ -503,7 +503,7 @@ void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double pa
     A.k = L.k;
     A.ldp = L.bmax;
     A.nranges = mfma ? (L.dp <= 128 ? bs_nranges(nb, bs_mode(precision), L.dp) : 0)
-                     : direct_nranges(nb, L.d, fp64);
+                     : direct_nranges(L, nb, fp64);
     A.RB = mfma ? 2 : direct_min_rows(L, A.nranges);
     A.kind = kind;
     A.param = param;
