@@ -70,14 +70,18 @@ void launch_cross_mfma(const Layout &L, const Buffers &B, int nb, int precision,
 void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64, int mfma,
                   int precision, double tie_delta, double ymax2, const RowOutputs &out, bool with_rank,
                   hipStream_t st);
+// Sum of the smallest distances of rows [0, nb): not taken, stored in or added
+// to obj[1].
+constexpr int kSumNone = 0, kSumStore = 1, kSumAdd = 2;
 // The rows that launch_score lists for re-scoring in the BF16 forms: every
 // such scoring is followed, before its results are used, by launch_rescore or
 // (with_rank) by an update that update_rescores admits, with the same arguments.
 RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precision, double kappa,
                          const RowOutputs &out, bool with_rank);
-void launch_rescore(const Layout &L, const RescoreArgs &R, hipStream_t st);
+// (sum, kSum*: of the rows' smallest distances, as launch_sum_mind's)
+void launch_rescore(const Layout &L, const RescoreArgs &R, int sum, double *obj, hipStream_t st);
 bool update_rescores(const Layout &L, int b, int gram_ta, int gram_te);  // (packed layouts)
-void launch_sum_mind(const Buffers &B, int nb, int accumulate, hipStream_t st);
+void launch_sum_mind(const Buffers &B, int nb, int sum, hipStream_t st);
 // Bound on the error of a self norm N_j of the Gaussian MFMA forms (FP32
 // kernel values summed in FP64), for row stride dp, max ||y||^2 and kappa.
 double selfnorm_error_bound(int dp, double ymax2, double kappa);

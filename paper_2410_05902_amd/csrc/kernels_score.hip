@@ -480,18 +480,63 @@ RescoreArgs rescore_args(const Layout &L, const Buffers &B, int nb, int precisio
     return R;
 }
 
-template <int LAYOUT>
-__global__ __launch_bounds__(kRescoreThreads) void k_rescore(const RescoreArgs A)
+// Sum of min distances of rows [0, nb) in FP64 (fixed order, as by 1024
+// threads); adds to obj[1] when accumulate, else stores.  NT threads, red: NT
+// doubles of LDS.
+template <int NT>
+__device__ __forceinline__ void sum_mind(int nb, const float *mind, double *obj, int accumulate, double *red)
 {
-    (void)rescore_listed<LAYOUT>(A, A.ctr[0]);
+    const int tid = threadIdx.x;
+    double s[1024 / NT];
+#pragma unroll
+    for (int q = 0; q < 1024 / NT; ++q) {
+        s[q] = 0.0;
+        for (int p = tid + q * NT; p < nb; p += 1024)
+            s[q] += (double)mind[p];
+    }
+    static_assert(NT == 1024 || NT == 512, "the first step of the tree is in the thread");
+    red[tid] = NT == 1024 ? s[0] : s[0] + s[1024 / NT - 1];
+    __syncthreads();
+    for (int h = NT / 2; h > 0; h >>= 1) {
+        if (tid < h)
+            red[tid] += red[tid + h];
+        __syncthreads();
+    }
+    if (tid == 0)
+        obj[1] = accumulate ? obj[1] + red[0] : red[0];
 }
 
-void launch_rescore(const Layout &L, const RescoreArgs &R, hipStream_t st)
+// SUM: the workgroup that finishes the listed rows also sums the distances (an
+// objective in chunks of 256 rows took 3 us a chunk more with launches of their
+// own, listed rows or not).
+template <int LAYOUT, bool SUM>
+__global__ __launch_bounds__(kRescoreThreads) void k_rescore(const RescoreArgs A, double *obj, int accumulate)
 {
-    if (L.packed)
-        hipLaunchKernelGGL(k_rescore<2>, dim3(kRescoreWGs), dim3(kRescoreThreads), 0, st, R);
-    else
-        hipLaunchKernelGGL(k_rescore<1>, dim3(kRescoreWGs), dim3(kRescoreThreads), 0, st, R);
+    const bool done = rescore_listed<LAYOUT>(A, A.ctr[0]);
+    if constexpr (SUM) {
+        __shared__ double red[kRescoreThreads];
+        if (done)  // workgroup uniform
+            sum_mind<kRescoreThreads>(A.nb, A.mind, obj, accumulate, red);
+    }
+}
+
+void launch_rescore(const Layout &L, const RescoreArgs &R, int sum, double *obj, hipStream_t st)
+{
+#define MBKK_RESC(LAYOUT, SUM)                                                                                       \
+    hipLaunchKernelGGL((k_rescore<LAYOUT, SUM>), dim3(kRescoreWGs), dim3(kRescoreThreads), 0, st, R, obj, \
+                       sum == kSumAdd)
+    if (L.packed) {
+        if (sum != kSumNone)
+            MBKK_RESC(2, true);
+        else
+            MBKK_RESC(2, false);
+    } else {
+        if (sum != kSumNone)
+            MBKK_RESC(1, true);
+        else
+            MBKK_RESC(1, false);
+    }
+#undef MBKK_RESC
 }
 
 void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double param, int fp64, int mfma,
@@ -557,30 +602,15 @@ void launch_score(const Layout &L, const Buffers &B, int nb, int kind, double pa
 #undef MBKK_SCORE
 }
 
-// Sum of min distances of rows [0, nb) in FP64 (fixed order); adds to obj[1]
-// when accumulate, else stores.
-__global__ __launch_bounds__(1024) void k_sum_mind(int nb, const float *__restrict__ mind,
-                                                    double *__restrict__ obj, int accumulate)
+__global__ __launch_bounds__(1024) void k_sum_mind(int nb, const float *mind, double *obj, int accumulate)
 {
     __shared__ double red[1024];
-    const int tid = threadIdx.x;
-    double s = 0.0;
-    for (int p = tid; p < nb; p += 1024)
-        s += (double)mind[p];
-    red[tid] = s;
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-        if (tid < h)
-            red[tid] += red[tid + h];
-        __syncthreads();
-    }
-    if (tid == 0)
-        obj[1] = accumulate ? obj[1] + red[0] : red[0];
+    sum_mind<1024>(nb, mind, obj, accumulate, red);
 }
 
-void launch_sum_mind(const Buffers &B, int nb, int accumulate, hipStream_t st)
+void launch_sum_mind(const Buffers &B, int nb, int sum, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_sum_mind, dim3(1), dim3(1024), 0, st, nb, B.mind, B.obj, accumulate);
+    hipLaunchKernelGGL(k_sum_mind, dim3(1), dim3(1024), 0, st, nb, B.mind, B.obj, sum == kSumAdd);
 }
 
 }  // namespace mbkk

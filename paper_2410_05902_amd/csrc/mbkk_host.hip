@@ -523,7 +523,8 @@ static bool step_rescores(const mbkk_ctx *c, int b)
     return c->L.bf16 && update_rescores(c->L, b, gram_task_rows(c->L, c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64));
 }
 
-static int cross_and_score(mbkk_ctx *c, int nb, const RowOutputs &out, bool with_rank)
+// sum (kSum*): of the rows' smallest distances, into the objective's scalar.
+static int cross_and_score(mbkk_ctx *c, int nb, const RowOutputs &out, bool with_rank, int sum)
 {
     const Layout &L = c->L;
     const mbkk_config &cf = c->cfg;
@@ -546,7 +547,9 @@ static int cross_and_score(mbkk_ctx *c, int nb, const RowOutputs &out, bool with
                  out, with_rank, c->stream);
     // rows listed for re-scoring: here, unless the update that follows runs them
     if (L.bf16 && !(with_rank && step_rescores(c, nb)))
-        launch_rescore(L, rescore_args(L, c->B, nb, cf.precision, cf.kernel_param, out, with_rank), c->stream);
+        launch_rescore(L, rescore_args(L, c->B, nb, cf.precision, cf.kernel_param, out, with_rank), sum, c->B.obj, c->stream);
+    else if (sum != kSumNone)
+        launch_sum_mind(c->B, nb, sum, c->stream);
     HIPCHK(c, hipGetLastError());
     return MBKK_OK;
 }
@@ -834,7 +837,7 @@ static int dp_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels
     out.labels = labels_dev;
     out.mind = mind_dev;
     launch_dp_score(L, B, cf.kernel, cf.kernel_param, c->fp64, B.batidx, b, true, out, nullptr, c->stream);
-    launch_sum_mind(B, b, 0, c->stream);
+    launch_sum_mind(B, b, kSumStore, c->stream);
     launch_dp_update(L, B, b, cf.kernel, cf.kernel_param, c->fp64, cf.lr, c->stream);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->timing) {
@@ -874,7 +877,7 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
     RowOutputs out;
     out.labels = labels_dev;
     out.mind = mind_dev;
-    int rc = cross_and_score(c, b, out, true);
+    int rc = cross_and_score(c, b, out, true, kSumNone);
     if (rc)
         return rc;
     // update of the centers
@@ -933,7 +936,7 @@ int mbkk_assign(mbkk_ctx *c, const int32_t *idx, int64_t m, int32_t *labels_dev,
                             c->cfg.validate ? B.flags : nullptr, c->stream);
         } else {
             prepare(c, idx + m0, nb);
-            int rc = cross_and_score(c, nb, out, false);
+            int rc = cross_and_score(c, nb, out, false, kSumNone);
             if (rc)
                 return rc;
         }
@@ -957,13 +960,13 @@ int mbkk_objective(mbkk_ctx *c, const int32_t *idx, int64_t m, double *out_host)
         if (L.untrunc) {
             launch_dp_score(L, c->B, c->cfg.kernel, c->cfg.kernel_param, c->fp64, idx + m0, nb, false, RowOutputs{},
                             c->cfg.validate ? c->B.flags : nullptr, c->stream);
+            launch_sum_mind(c->B, nb, m0 > 0 ? kSumAdd : kSumStore, c->stream);
         } else {
             prepare(c, idx + m0, nb);
-            int rc = cross_and_score(c, nb, RowOutputs{}, false);
+            int rc = cross_and_score(c, nb, RowOutputs{}, false, m0 > 0 ? kSumAdd : kSumStore);
             if (rc)
                 return rc;
         }
-        launch_sum_mind(c->B, nb, m0 > 0, c->stream);
     }
     return finish(c, out_host, 1, m);
 }
@@ -1142,8 +1145,9 @@ int mbkk_objective_fwd(mbkk_ctx *c, const float *xb_dev, int32_t b, double sigma
     launch_score(L, Bs, b, MBKK_GAUSS, kappa, c->fp64, c->use_mfma, cf.precision, tie_delta(cf), c->ymax2, out,
                  false, c->stream);
     if (L.bf16)
-        launch_rescore(L, rescore_args(L, Bs, b, cf.precision, kappa, out, false), c->stream);
-    launch_sum_mind(B, b, 0, c->stream);
+        launch_rescore(L, rescore_args(L, Bs, b, cf.precision, kappa, out, false), kSumStore, B.obj, c->stream);
+    else
+        launch_sum_mind(B, b, kSumStore, c->stream);
     HIPCHK(c, hipGetLastError());
     Scalars s;
     rc = read_scalars(c, &s);

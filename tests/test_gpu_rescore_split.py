@@ -86,6 +86,12 @@ def test_rescored_rows(n, d, k, win, rows, listed, parts):
         assert np.abs(a["D"].cpu().numpy()[:, :near] - D[:, :near]).max() <= eN + 1e-12
         assert np.abs(a["margin"].cpu().numpy() - ref["margin"]).max() <= 2.0 * eN + 2.0 ** -23
         assert m.rescore_count(reset=True) == rows
+    # the objective sums the re-scored rows' distances, in one chunk and over several
+    for R in (Q, np.resize(Q, 2 * b + 17)):
+        mind = m.assign(R)["mind"].double()
+        assert m.rescore_count(reset=True) == R.size
+        assert abs(m.objective(R) - float(mind.mean())) <= 1e-14
+        assert m.rescore_count(reset=True) == R.size
     out = m.step(Q, want_objective=True)
     lab = check(out)
     assert m.rescore_count(reset=True) == rows
