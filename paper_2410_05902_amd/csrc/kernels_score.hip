@@ -364,30 +364,48 @@ __global__ __launch_bounds__(64 * kScoreWaves) void k_score(const ScoreArgs A)
         uint64_t todo = __ballot(act && (double)fmar[lane] < fdel[lane]);
         if (__builtin_expect(todo != 0, 0)) {  // workgroup uniform
             const RescoreLds S{&sl[0][0], &sb[0][0], &ss[0][0], &flist[0]};
-            int nown = 0, room = kRescoreOwnEntries;
-            __syncthreads();  // the margins are read before the first row's is replaced
-            while (todo) {
-                const int r = __ffsll((unsigned long long)todo) - 1, rw = blockIdx.x * 64 + r;
-                todo &= todo - 1;
-                RescoreBest best;
-                double outside;
-                if (rescore_row<LAYOUT, true>(A.R, S, rw, fdel[r], fbest[r], RB, seg_off, Nv, 0, 0, 0, room, best,
-                                              outside)) {
-                    ++nown;
-                    if (threadIdx.x == 0) {
-                        flab[r] = best.l < A.k ? best.l : 0;
-                        fmin_[r] = (float)best.b;
-                        fmar[r] = (float)(fmin(best.s, outside) - best.b);
-                    }
-                } else if (threadIdx.x == 0) {
-                    // listed, with the approximate result standing in
+            int nown = 0;
+            // one thread's: a row's result, or its place in the list, with the
+            // approximate result standing in
+            auto publish = [&](int r, bool done, const RescoreBest &best, double outside) {
+                nown += done;
+                if (done) {
+                    flab[r] = best.l < A.k ? best.l : 0;
+                    fmin_[r] = (float)best.b;
+                    fmar[r] = (float)(fmin(best.s, outside) - best.b);
+                } else {
                     const int at = atomicAdd(&A.R.ctr[0], 1);
-                    A.R.list[at] = rw;
+                    A.R.list[at] = blockIdx.x * 64 + r;
                     A.R.delta[at] = fdel[r];
+                }
+            };
+            RescoreBest best;
+            double outside;
+            __syncthreads();  // the margins are read before the first row's is replaced
+            if (__popcll(todo) <= kRescoreTogether) {  // workgroup uniform
+                int room = kRescoreOwnEntries;
+                while (todo) {
+                    const int r = __ffsll((unsigned long long)todo) - 1;
+                    todo &= todo - 1;
+                    const bool done = rescore_row<LAYOUT, true>(A.R, S, blockIdx.x * 64 + r, fdel[r], fbest[r], RB,
+                                                                seg_off, Nv, 0, 0, 0, room, best, outside);
+                    if (threadIdx.x == 0)
+                        publish(r, done, best, outside);
+                }
+            } else {
+                for (int turn = 0; todo; ++turn) {
+                    const int r = __ffsll((unsigned long long)todo) - 1;
+                    todo &= todo - 1;
+                    if (turn % kScoreWaves != w)
+                        continue;  // another wave's
+                    const bool done = rescore_row_wave<LAYOUT>(A.R, blockIdx.x * 64 + r, fdel[r], fbest[r], RB, seg_off,
+                                                               Nv, best, outside);
+                    if (lane == 0)
+                        publish(r, done, best, outside);
                 }
             }
             __syncthreads();
-            if (threadIdx.x == 0 && nown > 0)
+            if (nown > 0)
                 atomicAdd(A.R.nresc, (unsigned long long)nown);
         }
     }

@@ -8,7 +8,7 @@
 // loads, and where a center has collapsed (a candidate of 10^4 entries) the
 // FP64 rate of the compute units at work on it.  So a row of little work is
 // done by the scoring workgroup that found it (kernels_score.hip), all 16 waves
-// together (3 us a row); a row of much work is listed for a later launch, the
+// together (3 us a row), or one wave each where it found many; a row of much work is listed for a later launch, the
 // update's own where the small one runs (kernels_prep.hip), else k_rescore, and
 // split over up to 16 of its workgroups.  (At most as many centers as the launch
 // has threads per workgroup, 512 in k_rescore: with more, a listed row is one
@@ -30,6 +30,11 @@ constexpr int kRescoreWGs = 256;      // workgroups that share the listed rows
 constexpr int kRescoreThreads = 512;  // threads of a k_rescore workgroup
 constexpr int kRescoreMaxCand = 16;   // most candidates of a row that is split
 constexpr int kRescoreMaxParts = 16;  // most workgroups per row
+// Rows of a scoring workgroup up to which it takes them one after another with all
+// its waves; more are taken a wave to a row.  (5000 x 64, k = 3, b = 256: 10 rows a
+// workgroup, 1000 entries each, 13 us a row by the workgroup, 48 us for up to 16 by
+// their waves; with 64 rows and 17 candidates 4.1 ms and 0.7 ms.)
+constexpr int kRescoreTogether = 4;
 // Candidate entries up to which the scoring workgroup takes a row itself, its
 // rows together: its 16 waves need about 12 us for that many, a chain of load
 // latencies, against 10 to 25 us for the listed rows of the launch, however many.
@@ -323,6 +328,77 @@ __device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreL
         }
     }
     __syncthreads();
+    return true;
+}
+
+// Row `row` by one wave, in the scoring workgroup: a lane per entry, so that 64
+// rows' loads are in flight and nothing is added over the lanes but a center's
+// sum.  A single row takes several times as long as by the whole workgroup, but 16
+// of them are done at a time.  Returns false, with nothing done, if the row is to
+// be listed; on true every lane holds the result.
+template <int LAYOUT>
+__device__ __forceinline__ bool rescore_row_wave(const RescoreArgs &A, int row, double delta, double best, int RB,
+                                                 const int32_t *__restrict__ seg_off, const double *__restrict__ Nv,
+                                                 RescoreBest &R, double &outside)
+{
+    const int lane = threadIdx.x & 63;
+    const f32x4 *x4 = (const f32x4 *)(A.bat32 + (int64_t)row * A.dp);
+    const int n4 = A.dp / 4;  // rows are zero past d up to the padded stride
+    auto approx = [&](int j) -> double {  // as the scoring pass had it
+        return j < A.k ? 1.0 - 2.0 * cross_of<float, LAYOUT>(A.part, A.ldp, row, j, seg_off, RB) + Nv[j] : INFINITY;
+    };
+    if (A.split) {
+        int nc = 0, ne = 0;
+        for (int j0 = 0; j0 < A.k; j0 += 64) {
+            const int j = j0 + lane;
+            const bool cand = j < A.k && approx(j) <= best + delta;
+            nc += __popcll(__ballot(cand));
+            ne += cand ? seg_off[j + 1] - seg_off[j] : 0;
+        }
+#pragma nounroll
+        for (int o = 32; o > 0; o >>= 1)
+            ne += __shfl_xor(ne, o);
+        if (nc <= kRescoreMaxCand && ne > kRescoreOwnEntries)
+            return false;
+    }
+    R = RescoreBest{};
+    outside = INFINITY;
+    for (int j0 = 0; j0 < A.k; j0 += 64) {
+        const double Dap = approx(j0 + lane);
+        const bool cand = j0 + lane < A.k && Dap <= best + delta;
+        if (!cand)
+            outside = fmin(outside, Dap);
+        uint64_t m = __ballot(cand);
+        while (m) {  // candidates in center order (wave uniform)
+            const int j = j0 + __ffsll((unsigned long long)m) - 1;
+            m &= m - 1;
+            double p = 0.0;
+            for (int s = seg_off[j] + lane; s < seg_off[j + 1]; s += 64) {
+                const double w = A.sup_w64[s];
+                if (w == 0.0)
+                    continue;
+                const f32x4 *y4 = (const f32x4 *)(A.pool32 + (int64_t)A.sup_row[s] * A.dp);
+                double d2 = 0.0;
+#pragma unroll 4
+                for (int t = 0; t < n4; ++t) {
+                    const f32x4 a = x4[t], c = y4[t];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const double v = (double)a[u] - (double)c[u];
+                        d2 = fma(v, v, d2);
+                    }
+                }
+                p += w * exp(-d2 / A.kappa);
+            }
+            const double D = 1.0 - 2.0 * wave_sum_f64(p) + Nv[j];
+            if (A.Dout && lane == 0)
+                A.Dout[(int64_t)row * A.ldD + j] = D;  // replaces the approximate value
+            R.take(D, j);
+        }
+    }
+#pragma nounroll
+    for (int o = 32; o > 0; o >>= 1)
+        outside = fmin(outside, __shfl_xor(outside, o));
     return true;
 }
 
