@@ -382,27 +382,27 @@ __global__ __launch_bounds__(64 * kScoreWaves) void k_score(const ScoreArgs A)
             RescoreBest best;
             double outside;
             __syncthreads();  // the margins are read before the first row's is replaced
-            if (__popcll(todo) <= kRescoreTogether) {  // workgroup uniform
-                int room = kRescoreOwnEntries;
-                while (todo) {
-                    const int r = __ffsll((unsigned long long)todo) - 1;
-                    todo &= todo - 1;
-                    const bool done = rescore_row<LAYOUT, true>(A.R, S, blockIdx.x * 64 + r, fdel[r], fbest[r], RB,
-                                                                seg_off, Nv, 0, 0, 0, room, best, outside);
-                    if (threadIdx.x == 0)
-                        publish(r, done, best, outside);
-                }
-            } else {
-                for (int turn = 0; todo; ++turn) {
-                    const int r = __ffsll((unsigned long long)todo) - 1;
-                    todo &= todo - 1;
-                    if (turn % kScoreWaves != w)
-                        continue;  // another wave's
-                    const bool done = rescore_row_wave<LAYOUT>(A.R, blockIdx.x * 64 + r, fdel[r], fbest[r], RB, seg_off,
-                                                               Nv, best, outside);
-                    if (lane == 0)
-                        publish(r, done, best, outside);
-                }
+            int room = kRescoreOwnEntries, how = kRescoreDone, rows = __popcll(todo);
+            while (todo) {  // workgroup uniform
+                const int r = __ffsll((unsigned long long)todo) - 1;
+                how = rescore_row<LAYOUT, true>(A.R, S, blockIdx.x * 64 + r, fdel[r], fbest[r], RB, seg_off, Nv, 0, 0,
+                                                0, rows, room, best, outside);
+                if (how == kRescoreWaves)
+                    break;
+                rows = how == kRescoreList ? rows - 1 : 1;  // the first row that isn't listed decides
+                todo &= todo - 1;
+                if (threadIdx.x == 0)
+                    publish(r, how == kRescoreDone, best, outside);
+            }
+            for (int turn = 0; todo; ++turn) {
+                const int r = __ffsll((unsigned long long)todo) - 1;
+                todo &= todo - 1;
+                if (turn % kScoreWaves != w)
+                    continue;  // another wave's
+                const bool done = rescore_row_wave<LAYOUT>(A.R, blockIdx.x * 64 + r, fdel[r], fbest[r], RB, seg_off,
+                                                           Nv, best, outside);
+                if (lane == 0)
+                    publish(r, done, best, outside);
             }
             __syncthreads();
             if (nown > 0)

@@ -8,15 +8,16 @@
 // loads, and where a center has collapsed (a candidate of 10^4 entries) the
 // FP64 rate of the compute units at work on it.  So a row of little work is
 // done by the scoring workgroup that found it (kernels_score.hip), all 16 waves
-// together (3 us a row), or one wave each where it found many; a row of much work is listed for a later launch, the
-// update's own where the small one runs (kernels_prep.hip), else k_rescore, and
-// split over up to 16 of its workgroups.  (At most as many centers as the launch
-// has threads per workgroup, 512 in k_rescore: with more, a listed row is one
-// workgroup's.)  That launch's chain is 20 us long, but it is the same for 1 and
-// for 30 rows.  (In the scoring kernel with one wave per row and a lane per entry,
-// a launch that re-scored any row took 35 us more, and up to 900 us with a
-// collapsed center; 1M x 128, k = 100, b = 4096.)  An entry's row is read by 16
-// lanes (whole 256-byte stretches), and one exp serves 64 entries.
+// together (3 us a row), or a wave to each where it has many that can't be listed; a
+// row of much work is listed for a later launch, the update's own where the small
+// one runs (kernels_prep.hip), else k_rescore, and split over up to 16 of its
+// workgroups.  (At most as many centers as the launch has threads per workgroup, 512
+// in k_rescore: with more, a listed row is one workgroup's.)  That launch's chain is
+// 20 us long, but it is the same for 1 and for 30 rows.  (In the scoring kernel with
+// one wave per row and a lane per entry, a launch that re-scored any row took 35 us
+// more, and up to 900 us with a collapsed center; 1M x 128, k = 100, b = 4096.)  An
+// entry's row is read by 16 lanes (whole 256-byte stretches), and one exp serves 64
+// entries.
 #pragma once
 
 #include "cross_layout.h"
@@ -30,11 +31,6 @@ constexpr int kRescoreWGs = 256;      // workgroups that share the listed rows
 constexpr int kRescoreThreads = 512;  // threads of a k_rescore workgroup
 constexpr int kRescoreMaxCand = 16;   // most candidates of a row that is split
 constexpr int kRescoreMaxParts = 16;  // most workgroups per row
-// Rows of a scoring workgroup up to which it takes them one after another with all
-// its waves; more are taken a wave to a row.  (5000 x 64, k = 3, b = 256: 10 rows a
-// workgroup, 1000 entries each, 13 us a row by the workgroup, 48 us for up to 16 by
-// their waves; with 64 rows and 17 candidates 4.1 ms and 0.7 ms.)
-constexpr int kRescoreTogether = 4;
 // Candidate entries up to which the scoring workgroup takes a row itself, its
 // rows together: its 16 waves need about 12 us for that many, a chain of load
 // latencies, against 10 to 25 us for the listed rows of the launch, however many.
@@ -159,21 +155,27 @@ __device__ __forceinline__ double rescore_entries(const RescoreArgs &A, const f3
     return wave_sum_f64(p);
 }
 
-// Smallest value over the workgroup, the same in every thread.
+// Smallest value of the 16 lanes of a DPP row.
+__device__ __forceinline__ double row_min_f64(double v)
+{
+    v = fmin(v, dpp_f64<0xb1>(v));     // quad_perm [1,0,3,2]
+    v = fmin(v, dpp_f64<0x4e>(v));     // quad_perm [2,3,0,1]
+    v = fmin(v, dpp_f64<0x141>(v));    // row_half_mirror
+    return fmin(v, dpp_f64<0x140>(v));  // row_mirror
+}
+
+// Smallest value over the workgroup (at most 16 waves), the same in every thread.
 __device__ __forceinline__ double rescore_min(double v, double *lds)
 {
-#pragma nounroll
-    for (int o = 32; o > 0; o >>= 1)
-        v = fmin(v, __shfl_xor(v, o));
+    v = row_min_f64(v);
+    v = fmin(v, __shfl_xor(v, 16));
+    v = fmin(v, __shfl_xor(v, 32));
     __syncthreads();
     if ((threadIdx.x & 63) == 0)
         lds[threadIdx.x >> 6] = v;
     __syncthreads();
-    v = lds[0];
-#pragma nounroll
-    for (int q = 1; q < (int)blockDim.x >> 6; ++q)
-        v = fmin(v, lds[q]);
-    return v;
+    const int q = threadIdx.x & 15;
+    return row_min_f64(lds[min(q, ((int)blockDim.x >> 6) - 1)]);
 }
 
 // The running (best, label, second) of a row.
@@ -207,16 +209,50 @@ struct RescoreLds {
     int *cnt;      // [kRescoreMaxWaves]
 };
 
-// Row `row`, by the whole workgroup.  SCORING: in the scoring workgroup;
-// returns false, with nothing done, if the row is to be listed: more candidate
-// entries than `room`, from which a row done is taken.  Else: listed
-// row q, of which this workgroup takes one part (of 1 << pl; all of it in part
-// 0 when pl = 0); returns false when the parts' sums are to be put together.
-// On true (part 0) thread 0 holds the result.
+// Whether `rows` rows like this one, of the nc candidates in S.cand, which may not
+// be listed, are better taken a wave to each (rescore_row_wave) than one after
+// another by the workgroup's waves, 2^lp to a candidate.  In microseconds, by the
+// stretches of 64 entries of a candidate: a row costs the workgroup 3.5 and the
+// longer of the latencies of its longest candidate's share and of its stretches'
+// work; a wave takes 10, and for each stretch dp / 8, its rows being read by single
+// lanes.  (10 to 17 rows of 16 stretches in one candidate of 3, 64 coordinates: 290
+// us by the workgroup, 160 us by waves; 784 coordinates: 650 and 1540 us.  64 rows of
+// 34 stretches in 8 candidates, 32 coordinates: 4.1 and 0.64 ms; 128 coordinates, 33 in
+// 2: 2.7 and 2.3 ms.)
+__device__ __forceinline__ bool rescore_by_waves(const RescoreArgs &A, const RescoreLds &S, int rows, int nc, int lp,
+                                                 const int32_t *__restrict__ seg_off)
+{
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    int sum = 0, top = 0;
+    for (int i = lane; i < nc; i += 64) {
+        const int n = (seg_off[S.cand[i] + 1] - seg_off[S.cand[i]] + 63) / 64;
+        sum += n;
+        top = max(top, n);
+    }
+#pragma nounroll
+    for (int o = 32; o > 0; o >>= 1) {
+        sum += __shfl_xor(sum, o);
+        top = max(top, __shfl_xor(top, o));
+    }
+    const float d = (float)A.dp;
+    const float row = 3.5f + fmaxf((float)((top + (1 << lp) - 1) >> lp) * (3.0f + 0.01f * d),
+                                   (float)sum * (1.1f + 0.0015f * d));
+    const float wave = 10.0f + (float)sum * fmaxf(4.0f, 0.125f * d) + 0.3f * (float)nc;
+    return (float)rows * row > (float)((rows + nw - 1) / nw) * wave;
+}
+
+// Row `row`, by the whole workgroup.  SCORING: in the scoring workgroup; with
+// nothing done, returns kRescoreList if the row is to be listed (more candidate
+// entries than `room`, from which a row done is taken), and kRescoreWaves if it
+// can't be and the `rows` rows from here on (1: not asked) are better taken a wave
+// to each.  Else: listed row q, of which this workgroup takes one part (of 1 << pl;
+// all of it in part 0 when pl = 0); returns kRescoreParts when the parts' sums are
+// to be put together.  On kRescoreDone (part 0) thread 0 holds the result.
+enum { kRescoreDone, kRescoreList, kRescoreWaves, kRescoreParts };
 template <int LAYOUT, bool SCORING>
-__device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreLds &S, int row, double delta,
+__device__ __forceinline__ int rescore_row(const RescoreArgs &A, const RescoreLds &S, int row, double delta,
                                             double best, int RB, const int32_t *__restrict__ seg_off,
-                                            const double *__restrict__ Nv, int q, int pl, int part, int &room,
+                                            const double *__restrict__ Nv, int q, int pl, int part, int rows, int &room,
                                             RescoreBest &R, double &outside)
 {
     const int lane = threadIdx.x & 63, nt = blockDim.x, nw = blockDim.x >> 6;
@@ -231,6 +267,7 @@ __device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreL
     // its own unless there is only one (the code is rarely run, so that its
     // length counts too: it comes from memory)
     const int np = (A.k + nt - 1) / nt;
+    int lanes = 64;  // of wave 0 that may hold a candidate's distance
     for (int ps = SCORING || np == 1 ? 0 : -np; ps < np; ++ps) {  // workgroup uniform; nt <= kRescoreChunk
         // the pass's candidates in center order
         const int jl = (ps < 0 ? ps + np : ps) * nt + threadIdx.x;
@@ -255,21 +292,25 @@ __device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreL
             S.cand[at + __popcll(m & ((1ull << lane) - 1ull))] = jl;
         __syncthreads();
         const bool split = !SCORING && pl > 0 && nc <= kRescoreMaxCand;  // (pl > 0: one pass)
-        if (SCORING && A.split && nc <= kRescoreMaxCand) {
-            int ne = 0;
-            for (int i = 0; i < nc; ++i)
-                ne += seg_off[S.cand[i] + 1] - seg_off[S.cand[i]];
-            if (ne > room)
-                return false;
-            room -= ne;
-        }
         if (!SCORING && !split && part > 0)
-            return false;
+            return kRescoreParts;
         // waves per candidate: all parts' (split), or all, a half, ... , one of
         // this workgroup's for 1, 2, 3-4, ... candidates
         int lp = 31 - __clz(nw);
         while (!split && lp > 0 && (nc << lp) > nw)
             --lp;
+        if constexpr (SCORING) {
+            if (A.split && nc <= kRescoreMaxCand) {
+                int ne = 0;
+                for (int i = 0; i < nc; ++i)
+                    ne += seg_off[S.cand[i] + 1] - seg_off[S.cand[i]];
+                if (ne > room)
+                    return kRescoreList;
+                room -= ne;
+            } else if (rows > 1 && ps == 0 && rescore_by_waves(A, S, rows, nc, lp, seg_off)) {
+                return kRescoreWaves;
+            }
+        }
         const int pt = split ? part * nw + w : w & ((1 << lp) - 1), waves = split ? nw << pl : 1 << lp;
         for (int ci = w >> lp; ci < nc; ci += nw >> lp) {  // wave uniform
             const int j = S.cand[ci];
@@ -295,9 +336,10 @@ __device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreL
                 }
             }
             __syncthreads();
-            return false;
+            return kRescoreParts;
         }
         __syncthreads();
+        lanes = np == 1 ? min(nc, 64) : 64;
         if (w == 0) {
             for (int ci = lane; ci < nc; ci += 64) {
                 const int j = S.cand[ci];
@@ -315,7 +357,7 @@ __device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreL
     outside = rescore_min(outside, S.min);
     if (w == 0) {
 #pragma nounroll
-        for (int o = 32; o > 0; o >>= 1) {
+        for (int o = 1; o < lanes; o <<= 1) {
             const double bq = __shfl_xor(R.b, o), sq = __shfl_xor(R.s, o);
             const int lq = __shfl_xor(R.l, o);
             if (lex_less(bq, lq, R.b, R.l)) {
@@ -328,7 +370,7 @@ __device__ __forceinline__ bool rescore_row(const RescoreArgs &A, const RescoreL
         }
     }
     __syncthreads();
-    return true;
+    return kRescoreDone;
 }
 
 // Row `row` by one wave, in the scoring workgroup: a lane per entry, so that 64
@@ -476,7 +518,7 @@ __device__ __forceinline__ bool rescore_listed(const RescoreArgs &A, int nrows)
         double outside;
         int room = 0;
         if (rescore_row<LAYOUT, false>(A, S, row, A.delta[q], INFINITY, RB, A.seg_off, A.N, q, pl,
-                                       t & ((1 << pl) - 1), room, R, outside) &&
+                                       t & ((1 << pl) - 1), 1, room, R, outside) == kRescoreDone &&
             threadIdx.x == 0) {
             rescore_result(A, row, R, outside);
             if (pl > 0)

@@ -26,8 +26,9 @@ def _constant(name, text):
 
 # rows: listed at once; parts of a row: the most (up to 16) that the 256 workgroups have for each
 @pytest.mark.parametrize("n,d,k,win,rows,listed,parts", [
-    # no room for the list's scratch: the scoring workgroups do all, 4 rows together, 5 a wave to each
-    (8191, 64, 3, 2, 40, False, 0), (8191, 64, 3, 2, 4, False, 0), (8191, 160, 3, 2, 5, False, 0),
+    # no room for the list's scratch: the scoring workgroups do all, a few rows one after
+    # another, many a wave to each (here from 7 rows on at 64 coordinates, from 58 at 160)
+    (8191, 64, 3, 2, 40, False, 0), (8191, 64, 3, 2, 4, False, 0), (8191, 160, 3, 2, 64, False, 0),
     (8191, 64, 600, 2, 70, False, 0),
     (8192, 64, 3, 2, 1, True, 16), (8192, 64, 3, 2, 16, True, 16), (8192, 64, 3, 2, 17, True, 8),
     (8192, 64, 3, 2, 128, True, 2), (8192, 64, 3, 2, 129, True, 1), (9000, 128, 16, 2, 1000, True, 1),
