@@ -929,27 +929,16 @@ __global__ __launch_bounds__(1024) void k_group_offsets(
 // chunk sums of the counts are split over kGroupThreads / k slices of chunks.
 constexpr int kGroupSmallK = 512, kGroupSmallC = 8, kGroupThreads = 1024;
 
-// RS: the rows that the scoring listed for re-scoring are finished first, by
-// every workgroup of the launch (rescore_listed), and one of them goes on: a
-// launch of their own would cost each step 3 us, listed rows or not.
-// (gcnt, mind, labels and rank aren't restrict: the re-scoring writes them.)
-template <bool RS>
-__global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
-    const RescoreArgs resc,
+__device__ __forceinline__ void group_offsets_small(
     int b, int k, int nchunk, int C, int p_new, int p_expired, int init_alive_before, int init_keep,
-    SlotList live, WindowRank win, int lr, const int32_t *gcnt, const float *mind,
-    double *__restrict__ coef, double *__restrict__ cum, int32_t *__restrict__ counts,
-    double *__restrict__ alpha, int32_t *__restrict__ off, double *__restrict__ obj,
-    const int32_t *labels, const int32_t *rank, const int32_t *__restrict__ pts,
+    const SlotList &live, const WindowRank &win, int lr, const int32_t *__restrict__ gcnt,
+    const float *__restrict__ mind, double *__restrict__ coef, double *__restrict__ cum,
+    int32_t *__restrict__ counts, double *__restrict__ alpha, int32_t *__restrict__ off, double *__restrict__ obj,
+    const int32_t *__restrict__ labels, const int32_t *__restrict__ rank, const int32_t *__restrict__ pts,
     int32_t *__restrict__ ring_idx, int32_t *__restrict__ ring_perm, uint32_t gram_mask, int gram_ta, int gram_te,
     int gram_qmax, int gram_nwaves, const int32_t *__restrict__ ring_off, int32_t *__restrict__ goff, int pad,
     int packed, int32_t *__restrict__ seg_next)
 {
-    if constexpr (RS) {
-        const int listed = resc.ctr[0];
-        if (__builtin_expect(listed > 0 || blockIdx.x != 0, 0) && !rescore_listed<2>(resc, listed))
-            return;
-    }
     constexpr int RPT = kMaxBatch / kGroupThreads;  // batch rows per thread
     // the task rows and columns are powers of two (the launch checks it)
     const int lta = __builtin_ctz((unsigned)gram_ta), lte = __builtin_ctz((unsigned)gram_te);
@@ -1071,12 +1060,18 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
     // ---- learning rate and the coefficient update of center j
     int tasks[kGramTileSteps] = {};  // Gram tasks of 1, 2, 4, ... column tiles
     int slen = 0;
-    // the slot's own row count where its column is counted, and the rows of the
-    // other counted columns (else 0)
-    int nown = 0, nel[kGroupSmallC];
+    // (gram_block_tasks in counts of slot-row blocks and column tiles, which are
+    // taken once: written out per column and step it cost the update 1 us)
+    // nA: slot-row blocks; ntl: column tiles of the counted columns but the slot's
+    // own (else 0); nto: of the own one
+    int nA = 0, nto = 0, ntl[kGroupSmallC];
 #pragma unroll
     for (int c = 0; c < kGroupSmallC; ++c)
-        nel[c] = 0;
+        ntl[c] = 0;
+    auto own_tasks = [&](int q) -> int {  // of 1 << q column tiles
+        const int nE = (nto + (1 << q) - 1) >> q;
+        return lte + q >= lta && nE > 0 ? (nE * (nE - 1) / 2 << max(lte + q - lta, 0)) + nA : nA * nE;
+    };
     if (own) {
         double a;
         if (lr == MBKK_LR_FULL)
@@ -1146,18 +1141,23 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
         for (int c = 0; c < kGroupSmallC; ++c) {
             if (c < C && ((gram_mask >> c) & 1u) && cf[c] != 0.0) {
                 const int nec = c == 0 ? 1 : (c - 1 == p_new ? bj : ne[c]);
-                const bool ownc = c - 1 == p_new;
-                nown = ownc ? bj : nown;
-                nel[c] = ownc ? 0 : nec;
-#pragma unroll
-                for (int qi = 0; qi < kGramTileSteps; ++qi)
-                    tasks[qi] += gram_block_tasks(bj, nel[c], lta, lte + qi, false);
+                const int nt = (nec + gram_te - 1) >> lte;
+                if (c - 1 == p_new)
+                    nto = nt;
+                else
+                    ntl[c] = nt;
                 slen += nec;
             }
         }
+        nA = (bj + gram_ta - 1) >> lta;
 #pragma unroll
-        for (int qi = 0; qi < kGramTileSteps; ++qi)
-            tasks[qi] += gram_block_tasks(bj, nown, lta, lte + qi, true);
+        for (int qi = 0; qi < kGramTileSteps; ++qi) {
+            int t = 0;
+#pragma unroll
+            for (int c = 0; c < kGroupSmallC; ++c)
+                t += (ntl[c] + (1 << qi) - 1) >> qi;
+            tasks[qi] = nA * t + own_tasks(qi);
+        }
         slen = seg_padded_len(slen, pad, packed);
     }
     int sv[1 + kGramTileSteps], srun_[1 + kGramTileSteps], stot[1 + kGramTileSteps];
@@ -1180,12 +1180,12 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
         seg_next[k] = seg_padded_end(stot[0], pad, packed);
     if (own) {
         int trun = srun_[1 + qi];
-        const int town = gram_block_tasks(bj, nown, lta, lte + qi, true);
+        const int town = own_tasks(qi);
 #pragma unroll
         for (int c = 0; c < kGroupSmallC; ++c) {
             if (c < C) {
                 goff[(int64_t)j * C + c] = trun;
-                trun += gram_block_tasks(bj, nel[c], lta, lte + qi, false) + (c - 1 == p_new ? town : 0);
+                trun += c - 1 == p_new ? town : nA * ((ntl[c] + Q - 1) >> qi);
             }
         }
     }
@@ -1230,6 +1230,31 @@ __global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
     }
 }
 
+// RS: the rows that the scoring listed for re-scoring are finished first, by
+// every workgroup of the launch (rescore_listed), and one of them goes on: a
+// launch of their own would cost each step 3 us, listed rows or not.
+// (gcnt, mind, labels and rank aren't restrict here: the re-scoring writes them.)
+template <bool RS>
+__global__ __launch_bounds__(kGroupThreads) void k_group_offsets_small(
+    int b, int k, int nchunk, int C, int p_new, int p_expired, int init_alive_before, int init_keep,
+    SlotList live, WindowRank win, int lr, const int32_t *gcnt, const float *mind,
+    double *__restrict__ coef, double *__restrict__ cum, int32_t *__restrict__ counts,
+    double *__restrict__ alpha, int32_t *__restrict__ off, double *__restrict__ obj,
+    const int32_t *labels, const int32_t *rank, const int32_t *__restrict__ pts,
+    int32_t *__restrict__ ring_idx, int32_t *__restrict__ ring_perm, uint32_t gram_mask, int gram_ta, int gram_te,
+    int gram_qmax, int gram_nwaves, const int32_t *__restrict__ ring_off, int32_t *__restrict__ goff, int pad,
+    int packed, int32_t *__restrict__ seg_next, const RescoreArgs resc)
+{
+    if constexpr (RS) {
+        const int listed = resc.ctr[0];
+        if (__builtin_expect(listed > 0 || blockIdx.x != 0, 0) && !rescore_listed<2>(resc, listed))
+            return;
+    }
+    group_offsets_small(b, k, nchunk, C, p_new, p_expired, init_alive_before, init_keep, live, win, lr, gcnt, mind,
+                        coef, cum, counts, alpha, off, obj, labels, rank, pts, ring_idx, ring_perm, gram_mask,
+                        gram_ta, gram_te, gram_qmax, gram_nwaves, ring_off, goff, pad, packed, seg_next);
+}
+
 static bool update_small(const Layout &L, int b, int gram_ta, int gram_te)
 {
     const bool pow2 = (gram_ta & (gram_ta - 1)) == 0 && (gram_te & (gram_te - 1)) == 0;
@@ -1257,12 +1282,13 @@ void launch_update(const Layout &L, const Buffers &B, int b, int p_new, int p_ex
                        (int)L.packed, B.seg_next)
 #define MBKK_GOS(RS)                                                                                              \
     hipLaunchKernelGGL(k_group_offsets_small<RS>, dim3(RS ? kRescoreWGs : 1), dim3(kGroupThreads), 0, st,         \
-                       RS ? *resc : RescoreArgs{}, b, L.k, nchunk, L.C, p_new, p_expired, init_alive_before,      \
+                       b, L.k, nchunk, L.C, p_new, p_expired, init_alive_before,                                  \
                        init_keep, live, win, lr, B.gcnt, B.mind, B.coef, B.cum, B.counts, B.alpha,                \
                        B.ring_off + (int64_t)p_new * (L.k + 1), B.obj, B.labels, B.rank,                          \
                        B.slot_pts + (int64_t)p_new * L.bmax, B.ring_idx + (int64_t)p_new * L.bmax,                \
                        B.ring_perm + (int64_t)p_new * L.bmax, gram_mask, gram_ta, gram_te, gram_qmax,             \
-                       gram_nwaves, B.ring_off, B.goff, L.pad, (int)L.packed, B.seg_next)
+                       gram_nwaves, B.ring_off, B.goff, L.pad, (int)L.packed, B.seg_next,                         \
+                       RS ? *resc : RescoreArgs{})
     if (update_small(L, b, gram_ta, gram_te)) {
         if (resc)
             MBKK_GOS(true);
