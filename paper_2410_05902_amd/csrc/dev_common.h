@@ -281,8 +281,8 @@ constexpr int kGramTA = 32, kGramTA64 = 16;
 // 32 rows took 13 us, 6.6 us so; b = 2048, k = 50: 16.8 -> 10.4; 16 coordinates
 // would lose it again on large slots, 8192 Laplacian rows, k = 100: 86 -> 90)
 constexpr int kGramTAShort = 8;
-// ... and of the MFMA form: two tiles of 16 x 16 per column tile at a fixed row
-// stride, one at a run-time one
+// ... and of the MFMA form: at most two tiles of 16 x 16 per column tile at a fixed
+// row stride (gram_task_rows), one at a run-time one
 constexpr int kGramTAMfma = 32, kGramTAMfmaWide = 16;
 // Column tiles per task that a plan may choose: 1, 2, ..., 2^(steps - 1).
 // A plan whose tasks outnumber the work kernel's waves takes more tiles per

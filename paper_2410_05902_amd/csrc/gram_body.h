@@ -13,6 +13,8 @@
 // gpart[w + jc] (the (wave, jc) runs form a staircase, so w + jc is distinct).
 #pragma once
 
+#include <type_traits>
+
 #include "dev_common.h"
 
 namespace mbkk {
@@ -23,6 +25,7 @@ struct GramWork {
     const int32_t *goff;  // [k*C + 1] task offsets
     double *gpart;        // [kGramWaves + k*C] per-run partials
     int nwaves;           // waves of the work kernel (sets the task ranges)
+    int ta;               // the plan's slot rows per task
 };
 
 constexpr int kGramWG = 256;  // 4 waves per workgroup
@@ -78,6 +81,7 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
     // whose waves have no task leaves once they have arrived
     const int T = A.goff[nJC];
     const int Q = TQ ? A.goff[nJC + 1] : 1;
+    const int lta = TQ ? __builtin_ctz((unsigned)A.ta) : __builtin_ctz(TA);
     const bool staged = nJC + 1 + nro <= kGramStage;  // workgroup uniform
     constexpr int SQ = kGramStage / kGramWG;
     const int tot = nJC + 1 + nro;
@@ -136,8 +140,8 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
         // the slot's own block, by the tasks on and above the diagonal: column
         // eb of tasks starts at task r eb (eb + 1) / 2 and holds the row blocks
         // up to r (eb + 1), its last r on the diagonal
-        const bool half = gram_half(c == 1 + A.rr, __builtin_ctz(TA), __builtin_ctz((unsigned)(TE * Q)));
-        const int r = max(1, TE * Q / TA);
+        const bool half = gram_half(c == 1 + A.rr, lta, __builtin_ctz((unsigned)(TE * Q)));
+        const int r = max(1, TE * Q >> lta);
         double lsum = 0.0;
         for (; t < e; ++t) {
             const int u = t - g0;
@@ -168,16 +172,15 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
 // ---------------------------------------------------------------------------
 // MFMA tasks (Gaussian): exp(-(||a||^2 + ||e||^2 - 2 a.e) / kappa) with a.e
 // on FP32 MFMA 16x16x4 (every MFMA form, the BF16 ones included): a task is
-// 32 slot rows (two row tiles; 16 at a run-time row stride) by Q tiles of 16
-// column rows (the plan's Q: at least 4, more when the tasks would outnumber
-// the waves).  Tiles of 16 keep the padding of a cluster of b_j rows small (a
+// 32 slot rows (two row tiles) or 16 (gram_task_rows; at a run-time row stride
+// always) by Q tiles of 16 column rows (the plan's Q: at least 4, more when the
+// tasks would outnumber the waves).  Tiles of 16 keep the padding of a cluster of b_j rows small (a
 // row tile past the cluster is skipped); the task loads its slot rows once
 // for all its column tiles, and each column tile's rows serve both row tiles:
 // what bounds it once a center has collapsed is the rows' way from L2 (4000 of
 // 4096 rows in one cluster, 128 coordinates, window 4: 293 us with one row tile,
-// 278 us so, 220 us with
-// the slot's own block halved, 198 us with the rows loaded as whole lines).  Lane l = 16 g + n supplies
-// A[n][g] (slot row n) and B[g][n] (column row n); the u-th MFMA of step t
+// 278 us so, 220 us with the slot's own block halved, 198 us with the rows loaded as
+// whole lines).  Lane l = 16 g + n supplies A[n][g] (slot row n) and B[g][n] (column row n); the u-th MFMA of step t
 // takes coordinate 16 t + 4 g + u, so one 16-byte load per lane and step
 // serves four MFMAs.  The lane holds D[4 g + i][n], i < 4.
 // DP = 0 takes the row stride at run time.  blk: the physical workgroup index.
@@ -188,16 +191,16 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                                                float c2, float c1, int blk)
 {
     const int dp = DP > 0 ? DP : dp_rt;
-    constexpr int NR = DP > 0 ? kGramTAMfma / 16 : kGramTAMfmaWide / 16;  // row tiles
-    __shared__ __attribute__((aligned(16))) float sqa[kGramWG / 64][NR][16];
+    constexpr int NRX = DP > 0 ? kGramTAMfma / 16 : kGramTAMfmaWide / 16;  // row tiles at most
+    __shared__ __attribute__((aligned(16))) float sqa[kGramWG / 64][NRX][16];
     // a wave's rows on their way to the products: a tile of 16 rows (run-time
     // row stride: 16 slot rows, then 16 column rows, of 32 coordinates), padded
     // by 4 coordinates
     __shared__ __attribute__((aligned(16))) float xch[kGramWG / 64][DP > 0 ? 16 : 32][(DP > 0 ? DP : 32) + 4];
     __shared__ int32_t stage[kGramStage];
     const int lane = threadIdx.x & 63, wl = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
-    gram_wave_loop<16 * NR, 16, true>(A, stage, blk, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int Q,
-                                                 double &lsum) {
+    auto task = [&](auto rows, const GramCol &a, const GramCol &ec, int ab, int eb, int Q, double &lsum) {
+        constexpr int NR = decltype(rows)::value;  // row tiles
         // the task: slot rows ab*16 NR.., column tiles tile0 .. tile1-1 (wave uniform)
         const int qa = ab * 16 * NR + n;
         const bool two = NR > 1 && qa - n + 16 < a.n;  // the second row tile holds rows
@@ -257,7 +260,8 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
         if constexpr (DP > 0) {
 #pragma unroll
             for (int r = 0; r < NR; ++r)
-                load_rows(ra_w[r], av[r]);
+                if (r == 0 || two)  // wave uniform
+                    load_rows(ra_w[r], av[r]);
         }
         // slot row n's norm for the output rows m, once per task
         auto publish_norms = [&]() {
@@ -314,12 +318,14 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                 const int tile = tile0 + t;
                 if (tile >= tile1)
                     break;  // wave uniform
-                const int tn = min(tile + 1, tile1 - 1);
-                const int64_t rn = col_row(tn, pes[t + 1 < QX ? t + 1 : t]);
-                const float sqn = poolsq[rn];
                 f32x4 ev[NS];
                 pass_rows(en, ev);
-                load_rows(rn, en);
+                float sqn = 0.0f;
+                if (tile + 1 < tile1) {  // wave uniform
+                    const int64_t rn = col_row(tile + 1, pes[t + 1 < QX ? t + 1 : t]);
+                    sqn = poolsq[rn];
+                    load_rows(rn, en);
+                }
                 f32x4 acc[NR];
 #pragma unroll
                 for (int r = 0; r < NR; ++r)
@@ -404,6 +410,13 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
                 tile_sum(tile, 0, acc, sqe_v);
             }
         }
+    };
+    gram_wave_loop<16 * NRX, 16, true>(A, stage, blk, [&](const GramCol &a, const GramCol &ec, int ab, int eb, int Q,
+                                                  double &lsum) {
+        if (NRX > 1 && A.ta > 16)  // launch uniform
+            task(std::integral_constant<int, NRX>{}, a, ec, ab, eb, Q, lsum);
+        else
+            task(std::integral_constant<int, 1>{}, a, ec, ab, eb, Q, lsum);
     });
 }
 

@@ -50,11 +50,13 @@ void launch_update(const Layout &L, const Buffers &B, int b, int p_new, int p_ex
 // by the update), then work and fold.  mfma: the Gaussian MFMA forms (FP32
 // MFMA products in every precision form); else VALU in FP64 or FP32.
 int gram_task_cols(int mfma, int fp64);  // te of the plan for the chosen Gram form
-int gram_task_rows(const Layout &L, int mfma, int fp64);  // ta of the plan for the chosen Gram form
+// ta of the plan for the chosen Gram form and a batch of b rows; launch_gram's
+// tasks have to be planned with the same b
+int gram_task_rows(const Layout &L, int mfma, int fp64, int b);
 int gram_task_qmax(int mfma);            // most column tiles per task the Gram form takes
 void launch_gram_plan(const Layout &L, const Buffers &B, int rr, uint32_t col_mask, int ta, int te, hipStream_t st);
 void launch_gram(const Layout &L, const Buffers &B, int rr, uint32_t col_mask, int kind, double param, int fp64,
-                 int mfma, bool fold, hipStream_t st);
+                 int mfma, int ta, bool fold, hipStream_t st);
 void launch_gram_fold(const Layout &L, const Buffers &B, int rr, uint32_t col_mask, int mfma, hipStream_t st);
 int gram_waves(int mfma);  // waves of the Gram work kernel of that form (its task ranges)
 

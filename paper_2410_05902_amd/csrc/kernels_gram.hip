@@ -261,11 +261,22 @@ int gram_task_cols(int mfma, int fp64)
     return mfma ? 16 : 64 * (fp64 ? gram_valu_rpl<double>() : gram_valu_rpl<float>());
 }
 
-int gram_task_rows(const Layout &L, int mfma, int fp64)
+// The MFMA form at a fixed row stride takes two row tiles per task where balanced
+// clusters (b / k rows) make more tasks of one than the chip has SIMDs: a column
+// tile's rows then serve both (128 coordinates, k = 100, b = 4096, 1500 tasks of one:
+// 12.0 us with one, 11.5 with two; half the batch in one center, 64 coordinates 113
+// and 101 us).  With fewer tasks, or clusters of at most one tile, one task's length
+// counts (96 coordinates, k = 50, b = 2048: 7.6 and 9.7 us; 128, k = 100, b = 300: 9.0
+// and 11.8; 32, k = 20, b = 1024: 6.4 and 7.3).
+int gram_task_rows(const Layout &L, int mfma, int fp64, int b)
 {
-    if (mfma)
-        return L.dp <= 128 ? kGramTAMfma : kGramTAMfmaWide;
-    return fp64 ? gram_valu_ta<double>(L.d) : gram_valu_ta<float>(L.d);
+    if (!mfma)
+        return fp64 ? gram_valu_ta<double>(L.d) : gram_valu_ta<float>(L.d);
+    if (L.dp > 128)
+        return kGramTAMfmaWide;
+    const int64_t rows = (b + L.k - 1) / L.k;
+    const int64_t tasks = (int64_t)L.k * (L.W + 1) * ((rows + 15) / 16) * ((rows + 63) / 64);
+    return rows <= 16 || tasks <= 1024 ? 16 : kGramTAMfma;
 }
 // the MFMA task loads its slot rows once for up to MBKK_GRAM_QMAX column
 // tiles (a power of two, at most 2^(kGramTileSteps - 1)); the VALU task
@@ -344,9 +355,10 @@ static void launch_gram_mfma(const Layout &L, const Buffers &B, const GramWork &
 }
 
 void launch_gram(const Layout &L, const Buffers &B, int rr, uint32_t mask, int kind, double param, int fp64,
-                 int mfma, bool fold, hipStream_t st)
+                 int mfma, int ta, bool fold, hipStream_t st)
 {
     GramWork A;
+    A.ta = ta;
     A.k = L.k;
     A.C = L.C;
     A.bmax = L.bmax;

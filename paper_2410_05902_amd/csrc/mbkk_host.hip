@@ -332,12 +332,12 @@ static uint32_t col_mask_of(const SlotList &s, bool init_alive)
 // the Gaussian MFMA forms (BF16 ones included), else VALU.  In a step
 // (`in_step`) the update kernel already wrote the task plan and the fold is
 // left to the next support layout; elsewhere plan, work and fold run here.
-static void gram(mbkk_ctx *c, int p, uint32_t mask, bool in_step)
+// ta: the plan's slot rows per task.
+static void gram(mbkk_ctx *c, int p, uint32_t mask, int ta, bool in_step)
 {
     if (!in_step)
-        launch_gram_plan(c->L, c->B, p, mask, gram_task_rows(c->L, c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64),
-                         c->stream);
-    launch_gram(c->L, c->B, p, mask, c->cfg.kernel, c->cfg.kernel_param, c->fp64, c->use_mfma, !in_step, c->stream);
+        launch_gram_plan(c->L, c->B, p, mask, ta, gram_task_cols(c->use_mfma, c->fp64), c->stream);
+    launch_gram(c->L, c->B, p, mask, c->cfg.kernel, c->cfg.kernel_param, c->fp64, c->use_mfma, ta, !in_step, c->stream);
     if (in_step) {
         c->fold_rr = p;
         c->fold_mask = mask;
@@ -520,7 +520,7 @@ static int timing_pair(mbkk_ctx *c, hipEvent_t *e0, hipEvent_t *e1)
 
 static bool step_rescores(const mbkk_ctx *c, int b)
 {
-    return c->L.bf16 && update_rescores(c->L, b, gram_task_rows(c->L, c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64));
+    return c->L.bf16 && update_rescores(c->L, b, gram_task_rows(c->L, c->use_mfma, c->fp64, b), gram_task_cols(c->use_mfma, c->fp64));
 }
 
 // sum (kSum*): of the rows' smallest distances, into the objective's scalar.
@@ -898,11 +898,12 @@ int mbkk_step(mbkk_ctx *c, const int32_t *batch, int32_t b, int32_t *labels_dev,
     for (int q = 0; q < live_after.n; ++q)
         win.rank[live_after.r[q]] = q;
     const bool resc = step_rescores(c, b);
+    const int ta = gram_task_rows(L, c->use_mfma, c->fp64, b);
     const RescoreArgs ra = resc ? rescore_args(L, B, b, c->cfg.precision, c->cfg.kernel_param, out, true) : RescoreArgs{};
     launch_update(L, B, b, p_new, p_expired, init_alive_before, init_keep, live, win, c->cfg.lr, mask,
-                  gram_task_rows(c->L, c->use_mfma, c->fp64), gram_task_cols(c->use_mfma, c->fp64), gram_task_qmax(c->use_mfma),
+                  ta, gram_task_cols(c->use_mfma, c->fp64), gram_task_qmax(c->use_mfma),
                   gram_waves(c->use_mfma), resc ? &ra : nullptr, c->stream);
-    gram(c, p_new, mask, true);
+    gram(c, p_new, mask, ta, true);
     c->seg_next_iter = i + 1;
     HIPCHK(c, hipGetLastError());
     c->slot_b[p_new] = b;
@@ -1342,7 +1343,7 @@ int mbkk_set_state(mbkk_ctx *c, const mbkk_state *s)
     // Gram blocks of every live slot against every live column
     for (int q = 0; q < live.n; ++q) {
         const int p = live.r[q];
-        gram(c, p, mask, false);
+        gram(c, p, mask, gram_task_rows(L, c->use_mfma, c->fp64, L.bmax), false);
     }
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));
