@@ -174,15 +174,16 @@ __device__ __forceinline__ void gram_wave_loop(const GramWork &A, int32_t *stage
 // on FP32 MFMA 16x16x4 (every MFMA form, the BF16 ones included): a task is
 // 32 slot rows (two row tiles) or 16 (gram_task_rows; at a run-time row stride
 // always) by Q tiles of 16 column rows (the plan's Q: at least 4, more when the
-// tasks would outnumber the waves).  Tiles of 16 keep the padding of a cluster of b_j rows small (a
-// row tile past the cluster is skipped); the task loads its slot rows once
-// for all its column tiles, and each column tile's rows serve both row tiles:
-// what bounds it once a center has collapsed is the rows' way from L2 (4000 of
-// 4096 rows in one cluster, 128 coordinates, window 4: 293 us with one row tile,
+// tasks would outnumber the waves).  Tiles of 16 keep the padding of a cluster of
+// b_j rows small (a row tile past the cluster is skipped); the task loads its slot
+// rows once for all its column tiles, and each column tile's rows serve both row
+// tiles: what bounds it once a center has collapsed is the rows' way from L2 (4000
+// of 4096 rows in one cluster, 128 coordinates, window 4: 293 us with one row tile,
 // 278 us so, 220 us with the slot's own block halved, 198 us with the rows loaded as
-// whole lines).  Lane l = 16 g + n supplies A[n][g] (slot row n) and B[g][n] (column row n); the u-th MFMA of step t
-// takes coordinate 16 t + 4 g + u, so one 16-byte load per lane and step
-// serves four MFMAs.  The lane holds D[4 g + i][n], i < 4.
+// whole lines).  Lane l = 16 g + n supplies A[n][g] (slot row n) and B[g][n]
+// (column row n); the u-th MFMA of step t takes coordinate 16 t + 4 g + u, so one
+// 16-byte load per lane and step serves four MFMAs.  The lane holds D[4 g + i][n],
+// i < 4.
 // DP = 0 takes the row stride at run time.  blk: the physical workgroup index.
 // ---------------------------------------------------------------------------
 template <int DP>
@@ -294,8 +295,7 @@ __device__ __forceinline__ void gram_mfma_work(const GramWork &A, int dp_rt, int
         };
         if constexpr (DP > 0) {
             // every tile's permutation entry at the start, then each tile's
-            // rows requested before the previous tile's products (clamped
-            // to the last tile, which then loads its rows twice)
+            // rows requested before the previous tile's products
             constexpr int QX = 1 << (kGramTileSteps - 1);
             int32_t pes[QX];
             pes[0] = pe;
